@@ -69,8 +69,8 @@ extern "C" {
                                       (rows that are not whole 16-byte
                                       strips: 128-bit access in the aligned
                                       strips around the row above 2048) */
-#define SOFTMAX_KERNEL_BLOCK_ROW 3 /* cols <= 16380 (NLL outputs: 32768):
-                                      one workgroup per row; also
+#define SOFTMAX_KERNEL_BLOCK_ROW 3 /* cols <= 16380: one workgroup per
+                                      row; also
                                       probability rows of 16385 to 24575
                                       columns in whole strips when the
                                       device has between 15/16 and 3 times
@@ -119,7 +119,7 @@ extern "C" {
  * Scratch: no entry point of this library allocates memory, so callers
  * that cannot allocate (code under stream capture, serving loops,
  * harnesses that forbid hipMalloc) can call any of them.  Rows longer than
- * 16380 columns (NLL outputs: 32768) are split over several workgroups
+ * 16380 columns are split over several workgroups
  * (except the block rows above),
  * which combine partial
  * (max, sum) pairs
@@ -256,13 +256,14 @@ SOFTMAX_API int softmax_log_fwd(const float* x, float* y, int64_t rows, int64_t 
  * (no row can have a valid label).
  *
  * Accuracy: |loss - loss*| <= 2e-6 + 2.5e-7 * (|loss*| + ln(cols)), as for
- * softmax_log_fwd.  Ownership, asynchrony, scratch (rows longer than
- * 32768 columns) and error codes follow softmax_fwd_clip, except that in
- * the one-pass long-row kernel a row's workgroups do not wait for each
- * other: the last to finish merges the row's partial pairs, writes the loss
- * and returns the row's exchange state to rest.  With 128-bit access
- * those rows are cut into chunks of 32768 columns (1024-thread workgroups)
- * rather than the chunks softmax_plan() reports for softmax_fwd.
+ * softmax_log_fwd.  Ownership, asynchrony, scratch and error codes follow
+ * softmax_fwd_clip, except that rows are streamed, at any length and
+ * alignment, by kernels of their own: only a few long rows (at most half as
+ * many as the device has compute units, and more than 32768 columns) are
+ * split over workgroups that meet in the exchange table, and there a row's
+ * workgroups do not wait for each other: the last to finish merges the
+ * row's partial pairs, writes the loss and returns the row's exchange state
+ * to rest.
  */
 SOFTMAX_API int softmax_nll_fwd(const float* x, const int64_t* labels, float* loss,
                                 int64_t rows, int64_t cols, float clip_lo,

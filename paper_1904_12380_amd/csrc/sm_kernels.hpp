@@ -8,8 +8,8 @@
 // kernel argument (default -64; no clip runs as the floor bound with a
 // clipped value of 0).  The MODE template argument says how the exponential
 // is evaluated (accurate, accurate into the denormal range, or the fast
-// approximation) or what is written instead of y: its logarithm, or one
-// negative log-likelihood per row.  Unlike the CPU functor, no kernel uses
+// approximation) or what is written instead of y: its logarithm, or (k_packed
+// only; longer rows are in sm_nll.hpp) one negative log-likelihood per row.  Unlike the CPU functor, no kernel uses
 // y as scratch: x is read from HBM once (twice for rows over 2^21 columns)
 // and y is written once.
 //
@@ -21,7 +21,7 @@
 //                 reduce one row each with DPP, and the tile goes back out
 //                 with 128-bit stores; the next tile's loads are issued early.
 //   k_wave_row    cols <= 4096: one wavefront per row, the row held in VGPRs.
-//   k_block_row   cols <= 8192 (32768 for log and NLL outputs): one
+//   k_block_row   cols <= 16380 (32768 through a caller's plan): one
 //                 workgroup per row, the row held in VGPRs, per-wave
 //                 partials combined through LDS.
 //   k_split_onepass   rows of up to 64 chunks: one workgroup per chunk,
@@ -478,82 +478,6 @@ __device__ __forceinline__ void store_online(float (&v)[4 * V],
     store_strip<V, VEC4>(v, [](float ev) { return ev; }, p, lane_off, stride, lim);
 }
 
-// The row's label as a column of the segment [c0, c0 + lim), or -1 when it
-// lies outside the segment (or outside the row).
-__device__ __forceinline__ int seg_label(int64_t label, int64_t c0, int lim) {
-  const int64_t l = label - c0;
-  return (l >= 0 && l < lim) ? static_cast<int>(l) : -1;
-}
-
-// Index into this lane's v (laid out as in load_strip) of segment column
-// lc, or -1 when this lane does not hold it (or lc < 0).
-template <int V, bool VEC4>
-__device__ __forceinline__ int held_index(int lc, int lane_off, int stride) {
-  if (lc < 0) return -1;
-  const int t = (VEC4 ? lc >> 2 : lc) - lane_off;
-  if (t < 0 || t % stride != 0) return -1;
-  const int i = t / stride;
-  if constexpr (VEC4) {
-    return i < V ? 4 * i + (lc & 3) : -1;
-  } else {
-    return i < 4 * V ? i : -1;
-  }
-}
-
-// What a lane contributes to an NLL output: the label's logit, if this lane
-// holds its column (`found`), and whether it must write NaN for a label
-// outside the row (`bad`: one thread of the row's first segment).
-struct LabelPick {
-  float x;
-  bool found;
-  bool bad;
-};
-
-// Picks the label's logit out of this lane's v (laid out as in load_strip)
-// for the segment [c0, c0 + lim).  Taken right after the loads, so that v
-// need not stay live through the row reductions.  Other modes pick nothing.
-template <int V, bool VEC4, int MODE>
-__device__ __forceinline__ LabelPick pick_label(const float (&v)[4 * V], int64_t label,
-                                                int64_t cols, int64_t c0, int lim, int lane_off,
-                                                int stride, bool first) {
-  LabelPick p{0.0f, false, false};
-  if constexpr (MODE == kNllOut) {
-    const int idx = held_index<V, VEC4>(seg_label(label, c0, lim), lane_off, stride);
-#pragma unroll
-    for (int i = 0; i < 4 * V; ++i) p.x = idx == i ? v[i] : p.x;
-    p.found = idx >= 0;
-    p.bad = first && (label < 0 || label >= cols);
-  }
-  return p;
-}
-
-// The output step of the segment [c0, c0 + lim) of `row`: the row's
-// outputs (probabilities or logs) into y + row * cols + c0, or for NLL
-// outputs the one loss y[row] = ln S - c_label, written by the lane that
-// picked the label's logit (NaN for a label outside [0, cols)).
-template <int V, bool VEC4, int MODE>
-__device__ __forceinline__ void finish_row(const float (&v)[4 * V], RowShift rs, float s,
-                                           float* y, int64_t row, int64_t cols, int64_t c0,
-                                           int lim, LabelPick pick, int lane_off, int stride) {
-  if constexpr (MODE == kNllOut) {
-    if (pick.found) y[row] = -log_out(pick.x, rs, log_of_sum(s));
-    if (pick.bad) y[row] = __builtin_nanf("");
-  } else {
-    store_row<V, VEC4, MODE>(v, rs, s, y + row * cols + c0, lane_off, stride, lim);
-  }
-}
-
-// The label of `row` for NLL outputs (0 in the other modes, where labels
-// is null).
-template <int MODE>
-__device__ __forceinline__ int64_t row_label(const int64_t* labels, int64_t row) {
-  if constexpr (MODE == kNllOut) {
-    return labels[row];
-  } else {
-    return 0;
-  }
-}
-
 // Columns of a row segment that starts at column c0: min(cols - c0, cap).
 __device__ __forceinline__ int seg_len(int64_t cols, int64_t c0, int64_t cap) {
   const int64_t left = cols - c0;
@@ -799,8 +723,7 @@ constexpr int kRowWaves = (V <= 8 && VEC4 && !keeps_logits<MODE>()) ? 4 : 2;
 template <int V, bool VEC4, int MODE, bool PH = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
     kRowWaves<V, VEC4, MODE>))) void k_wave_row(
-    const float* x, float* y, const int64_t* labels, int64_t rows, int64_t cols, Clip clip,
-    uint32_t delay) {
+    const float* x, float* y, int64_t rows, int64_t cols, Clip clip, uint32_t delay) {
   static_assert(!PH || (VEC4 && !keeps_logits<MODE>()), "phase access: probability outputs");
   const uint64_t t0 = wall_clock();
   const int lane = __lane_id();
@@ -808,7 +731,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
   for (int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + wave; row < rows;
        row += static_cast<int64_t>(gridDim.x) * 4) {
     const float* xr = x + row * cols;
-    const int64_t label = row_label<MODE>(labels, row);
     const int lim = static_cast<int>(cols);
     float v[4 * V];
     if constexpr (PH) {
@@ -823,11 +745,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
       continue;
     }
     load_strip<V, VEC4>(v, xr, opaque(lane), 64, lim);
-    const LabelPick pick = pick_label<V, VEC4, MODE>(v, label, cols, 0, lim, lane, 64, lane == 0);
     const RowShift rs = row_shift(seg_max<64>(array_max(v)), clip);
     const float s = seg_sum<64>(exp_strip<MODE>(v, rs));
     if (delay != 0) wait_until_after(t0 + delay, s);
-    finish_row<V, VEC4, MODE>(v, rs, s, y, row, cols, 0, lim, pick, opaque(lane), 64);
+    store_row<V, VEC4, MODE>(v, rs, s, y + row * cols, opaque(lane), 64, lim);
   }
 }
 
@@ -835,8 +756,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
 // (c) One workgroup of NT threads per row, cols <= 4*V*NT.  `delay` and PH
 // as for k_wave_row.
 template <int NT, int V, bool VEC4, int MODE, bool PH = false>
-__global__ __launch_bounds__(NT) void k_block_row(const float* x, float* y,
-                                                  const int64_t* labels, int64_t rows,
+__global__ __launch_bounds__(NT) void k_block_row(const float* x, float* y, int64_t rows,
                                                   int64_t cols, Clip clip, uint32_t delay) {
   static_assert(!PH || (VEC4 && !keeps_logits<MODE>()), "phase access: probability outputs");
   const uint64_t t0 = wall_clock();
@@ -846,7 +766,6 @@ __global__ __launch_bounds__(NT) void k_block_row(const float* x, float* y,
   const int tid = threadIdx.x;
   for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
     const float* xr = x + row * cols;
-    const int64_t label = row_label<MODE>(labels, row);
     const int lim = static_cast<int>(cols);
     float v[4 * V];
     if constexpr (PH) {
@@ -858,31 +777,10 @@ __global__ __launch_bounds__(NT) void k_block_row(const float* x, float* y,
       const float rcp = 1.0f / s;
       store_strip_ph<V>(v, [&](float ev) { return ev * rcp; }, y + row * cols, a, opaque(tid),
                         NT, lim);
-    } else if constexpr (MODE == kNllOut && VEC4) {
-      // The loss needs only the row's (max, sum) and one logit.  The sums
-      // are folded in as the loads land, and thread 0 reads the label's
-      // logit itself (one more cache line per row), so no value has to stay
-      // live after its exponential: two workgroups per CU still fit.  (With
-      // 32-bit loads the fold needs more registers than that; those rows
-      // take the reduction below.)
-      // The row's loads go out first; the logit's load waits only for the
-      // label, and is issued by every thread (one cache line per wavefront)
-      // so that no branch makes the compiler wait for all of them.
-      load_strip_flat<V, VEC4>(v, xr, tid, NT, lim);
-      const bool bad = label < 0 || label >= cols;
-      const float xl = xr[bad ? 0 : label];
-      const float2 ms = lane_online(v, clip);
-      const float m = block_max<NW>(ms.x, red_max);
-      const float s =
-          block_sum<NW>(lane_share(ms, row_shift(m == kNegInf ? 0.0f : m, clip)), red_sum);
-      if (tid == 0)
-        y[row] = bad ? __builtin_nanf("") : -log_out(xl, row_shift(m, clip), log_of_sum(s));
     } else {
       // (The online reduction of the split kernel measured slower here:
       // 23.2 us against 22.5 us on 512 rows of 32768.)
       load_strip<V, VEC4>(v, xr, opaque(tid), NT, lim);
-      const LabelPick pick =
-          pick_label<V, VEC4, MODE>(v, label, cols, 0, lim, tid, NT, tid == 0);
       const RowShift rs = row_shift(block_max<NW>(array_max(v), red_max), clip);
       // Log outputs of 32 values per lane keep the accurate exponential: with
       // the cheap one the compiler keeps more terms in flight, which needs
@@ -890,7 +788,7 @@ __global__ __launch_bounds__(NT) void k_block_row(const float* x, float* y,
       constexpr int SE = (MODE == kLogOut && V >= 8) ? kExpAccurate : kSumExp;
       const float s = block_sum<NW>(exp_strip<MODE, 4 * V, SE>(v, rs), red_sum);
       if (delay != 0) wait_until_after(t0 + delay, s);
-      finish_row<V, VEC4, MODE>(v, rs, s, y, row, cols, 0, lim, pick, opaque(tid), NT);
+      store_row<V, VEC4, MODE>(v, rs, s, y + row * cols, opaque(tid), NT, lim);
     }
   }
 }
@@ -1018,8 +916,7 @@ __global__ __launch_bounds__(NT) void k_split_stats(const float* x, XchArgs xa, 
 }
 
 template <int NT, int V, bool VEC4, int MODE>
-__global__ __launch_bounds__(NT) void k_split_apply(const float* x, float* y,
-                                                    const int64_t* labels, XchArgs xa,
+__global__ __launch_bounds__(NT) void k_split_apply(const float* x, float* y, XchArgs xa,
                                                     int64_t cols, int wpr, int64_t chunks,
                                                     Clip clip) {
   const uint64_t t0 = wall_clock();
@@ -1030,7 +927,6 @@ __global__ __launch_bounds__(NT) void k_split_apply(const float* x, float* y,
   const int b = blockIdx.x;
   const int lrow = b / wpr;
   const int w = b - lrow * wpr;
-  const int64_t label = row_label<MODE>(labels, lrow);
   uint64_t* entry = nullptr;  // wavefront 0 only
   if (tid < 64) {
     entry = wave_entry(xa, lrow, t0 + xa.limit_ticks);
@@ -1058,9 +954,7 @@ __global__ __launch_bounds__(NT) void k_split_apply(const float* x, float* y,
 #pragma unroll
       for (int i = 0; i < 4 * V; ++i) v[i] = exp_shift_clip<MODE>(v[i], rs);
     }
-    const LabelPick pick =
-        pick_label<V, VEC4, MODE>(v, label, cols, c0, lim, tid, NT, g == 0 && tid == 0);
-    finish_row<V, VEC4, MODE>(v, rs, srow, y, lrow, cols, c0, lim, pick, tid, NT);
+    store_row<V, VEC4, MODE>(v, rs, srow, y + lrow * cols + c0, tid, NT, lim);
   }
   if (entry != nullptr && tid < 64) {
     // The slot reads have returned (the outputs above depend on them).
@@ -1108,9 +1002,6 @@ __global__ __launch_bounds__(NT) void k_split_apply(const float* x, float* y,
 // HBM serves the reads and the writes of the launch in two phases instead of
 // interleaving them.
 //
-// NLL outputs (one value per row) take no wait at all: the last workgroup
-// of the row to depart does the merge.
-//
 // PH (probability outputs): rows whose length is not a multiple of 4, in
 // 16-byte aligned x and y.  Chunk g then covers the row's columns
 // [g*CH - a, (g+1)*CH - a) (clamped to the row), a = the row's phase, so
@@ -1121,8 +1012,7 @@ __global__ __launch_bounds__(NT) void k_split_apply(const float* x, float* y,
 template <int NT, int V, bool VEC4, int MODE, bool PH = false>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
     2 * kRowWaves<V, VEC4, MODE>))) void k_split_onepass(
-    const float* x, float* y, const int64_t* labels, XchArgs xa, int64_t cols, int chunks,
-    uint32_t delay, Clip clip) {
+    const float* x, float* y, XchArgs xa, int64_t cols, int chunks, uint32_t delay, Clip clip) {
   static_assert(!PH || (VEC4 && !keeps_logits<MODE>()), "phase access: probability outputs");
   const uint64_t t0 = wall_clock();
   constexpr int NW = NT / 64;
@@ -1147,7 +1037,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
     a = g == 0 ? ra : 0;
   }
   const float* xr = x + lrow * cols + c0;
-  const int64_t label = row_label<MODE>(labels, lrow);
 
   constexpr bool ONLINE = !keeps_logits<MODE>() && online_exp<4 * V>();
   static_assert(!PH || ONLINE, "phase access: the online reduction");
@@ -1163,65 +1052,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
   } else {
     load_strip<V, VEC4>(v, xr, tid, NT, lim);
   }
-  // NLL outputs: every workgroup reads the row's label logit right after its
-  // chunk's loads (one cache line per wavefront, after the label itself),
-  // so the one that merges the row below already holds it, and the values
-  // die as they are folded in.
-  const bool bad_label = label < 0 || label >= cols;
-  float xl = 0.0f;
-  if constexpr (MODE == kNllOut) xl = x[lrow * cols + (bad_label ? 0 : label)];
-  LabelPick pick{0.0f, false, false};
-  if constexpr (MODE == kLogOut)
-    pick = pick_label<V, VEC4, MODE>(v, label, cols, c0, lim, tid, NT, g == 0 && tid == 0);
   if constexpr (!ONLINE) part = chunk_partial<NW, V, MODE>(v, lim, clip, red_max, red_sum);
   const float m = part.x;
   const float s = part.y;
   const uint64_t deadline = t0 + xa.limit_ticks;
-
-  if constexpr (MODE == kNllOut) {
-    // One value per row: no workgroup waits.  Each publishes its pair and
-    // then counts itself out; the slot store has completed before the count
-    // (explicit wait), so the workgroup that brings the count to G sees all
-    // G pairs.  That one merges them as above, writes the loss with the
-    // label logit it read at the start, and frees the entry.
-    if (tid < 64) {
-      uint64_t* const entry = wave_entry(xa, lrow, deadline);
-      if (entry == nullptr) {
-        if (tid == 0) y[lrow] = __builtin_nanf("");
-        return;
-      }
-      uint64_t* const slots = entry_slots(entry);
-      uint32_t last = 0;
-      if (tid == 0) {
-        xch::st_agent(&slots[g], encode_pair(m, s));
-        __builtin_amdgcn_s_waitcnt(0);
-        last = depart_entry(entry, chunks, 1u) ? 1u : 0u;
-      }
-      last = __builtin_amdgcn_readfirstlane(last);
-      if (last) {
-        // Every pair was stored before its count, so none should read
-        // empty; a slot that still does is read again (bounded), so the
-        // merge does not rest on when a completed store becomes visible.
-        bool ok = true;
-        const uint64_t q = poll_slots(slots, chunks, deadline, &ok);
-        const float2 ms = tid < chunks ? make_float2(decode_m(q), decode_s(q))
-                                       : make_float2(kNegInf, 0.0f);
-        const float2 rowms = merge_lanes<kExpAccurate>(ms.x, ms.y, clip);
-        const float loss = (bad_label || !ok)
-                               ? __builtin_nanf("")
-                               : -log_out(xl, row_shift(rowms.x, clip), log_of_sum(rowms.y));
-        if (tid == 0) {
-          y[lrow] = loss;
-          if (!ok) count_give_up(xa, xch::kDiagWaitGiveUps);
-        }
-        // The slot reads have returned (the loss depends on them).
-        asm volatile("" : : "v"(loss));
-        if (tid < chunks) xch::st_agent(&slots[tid], 0ull);
-        if (tid == 0) release_entry(entry);
-      }
-    }
-    return;
-  }
 
   if (tid < 64) {
     uint64_t* const entry = wave_entry(xa, lrow, deadline);
@@ -1267,8 +1101,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
   if (delay != 0) wait_until(t0 + delay);
   if constexpr (keeps_logits<MODE>()) {
     // v still holds the logits: y = c - ln S against the row's M.
-    finish_row<V, VEC4, MODE>(v, row_shift(bcast[0], clip), bcast[1], y, lrow, cols, c0, lim,
-                              pick, tid, NT);
+    store_row<V, VEC4, MODE>(v, row_shift(bcast[0], clip), bcast[1], y + lrow * cols + c0, tid,
+                             NT, lim);
   } else if constexpr (ONLINE) {
     store_online<V, VEC4, MODE, PH>(v, mk, row_shift(bcast[0], clip), bcast[1],
                                     y + lrow * cols + c0, opaque(tid), NT, lim, a);

@@ -12,6 +12,7 @@
 #include "../../include/softmax_mi355x.h"
 #include "sm_host.hpp"
 #include "sm_kernels.hpp"
+#include "sm_nll.hpp"
 
 // The exchange table of rows split over several workgroups (layout in
 // sm_exchange.hpp).  The kernels claim and free its row entries themselves,
@@ -57,8 +58,7 @@ constexpr int kBlockThreads = 1024;
 // of 16384 to 32768 columns ran 22.3-22.5 us split against 24.2-26.7 us in
 // one workgroup.  Rows of 16381 to 16383 columns that are not whole strips
 // keep the split kernel (16383: 28.0 us split with 32-bit access against
-// 30.6 in one workgroup).  NLL rows keep k_block_row up to
-// kBlockRowMaxCols.
+// 30.6 in one workgroup).
 constexpr int64_t kSplitMinColsProb = 16380;
 // k_group_rows: when one workgroup per row block would take more than one
 // but at most this many rounds of the resident workgroups, the grid is
@@ -99,16 +99,13 @@ constexpr int64_t kGroupRowsOneStepDen = 10;
 // Split rows, one pass: a row spans at most this many workgroups (the
 // exchange is read by one wavefront, one slot per lane).  Chunk shapes,
 // threads x 4-element strips per lane: probability and log rows take 256 x 8
-// (8192 columns) up to kSmallChunkMaxChunks chunks; then every mode takes
+// (8192 columns) up to kSmallChunkMaxChunks chunks; then they take
 // 512 x 8 (16384 columns) up to 64 chunks, then 512 x 16 (32768, 128-bit
 // access only: with 32-bit access it would spill).  Measured per 64 MiB:
 // 256 x 8 ran 21.6-21.8 us on rows of 16384 to 65536 columns against
 // 21.8-22.7 for 512 x 8, but 22.5 against 21.7 on 131072 columns and 24.2
 // against 22.0 on 262144 (the row's wait for 16 or 32 partials costs more
-// than the smaller workgroups gain).  NLL outputs take 512 x 8 from the
-// first chunk: their workgroups never wait for each other and keep no
-// values; 1024 x 8 (32768 columns) measured 3-4% slower on 131072 to 524288
-// columns (64 x 262144: 15.9 against 15.3 us).
+// than the smaller workgroups gain).
 constexpr int64_t kOnePassMaxChunks = 64;
 constexpr int64_t kSmallChunkMaxChunks = 8;
 // Probability rows past kSmallChunkMaxChunks 8192-column chunks take
@@ -327,6 +324,23 @@ const void* group_rows_fn(int g) {
 }
 
 template <int EM, bool VEC4>
+const void* packed_shape_fn(const Shape& s) {
+  if (s.g == 1) return packed_fn<1, VEC4, EM>(s.epl, std::make_integer_sequence<int, 16>{});
+  if (s.g == 2) return packed_fn<2, VEC4, EM>(s.epl, std::make_integer_sequence<int, 8>{});
+  if (s.g == 4) return packed_fn<4, VEC4, EM>(s.epl, std::make_integer_sequence<int, 8>{});
+  if constexpr (EM == kExpAccurate || EM == kExpWide || EM == kExpFast) {
+    if (s.g == 8) return packed_fn<8, VEC4, EM>(s.epl, std::make_integer_sequence<int, 8>{});
+    if (s.g == 16) return packed_fn<16, VEC4, EM>(s.epl, std::make_integer_sequence<int, 8>{});
+  }
+  return nullptr;
+}
+
+template <int EM>
+const void* packed_mode(const Shape& s) {
+  return s.vec4 ? packed_shape_fn<EM, true>(s) : packed_shape_fn<EM, false>(s);
+}
+
+template <int EM, bool VEC4>
 const void* shape_fn(const Shape& s, bool stats_pass) {
   auto cast = [](auto f) { return reinterpret_cast<const void*>(f); };
   switch (s.kernel) {
@@ -337,15 +351,7 @@ const void* shape_fn(const Shape& s, bool stats_pass) {
       }
       return nullptr;
     case SOFTMAX_KERNEL_PACKED:
-      if (s.g == 1) return packed_fn<1, VEC4, EM>(s.epl, std::make_integer_sequence<int, 16>{});
-      if (s.g == 2) return packed_fn<2, VEC4, EM>(s.epl, std::make_integer_sequence<int, 8>{});
-      if (s.g == 4) return packed_fn<4, VEC4, EM>(s.epl, std::make_integer_sequence<int, 8>{});
-      if constexpr (EM == kExpAccurate || EM == kExpWide || EM == kExpFast) {
-        if (s.g == 8) return packed_fn<8, VEC4, EM>(s.epl, std::make_integer_sequence<int, 8>{});
-        if (s.g == 16)
-          return packed_fn<16, VEC4, EM>(s.epl, std::make_integer_sequence<int, 8>{});
-      }
-      return nullptr;
+      return packed_shape_fn<EM, VEC4>(s);
     case SOFTMAX_KERNEL_WAVE_ROW:
       if (s.ph) {
         if constexpr (VEC4 && (EM == kExpAccurate || EM == kExpWide || EM == kExpFast)) {
@@ -421,7 +427,7 @@ const void* kernel_fn(const Shape& s, int em, bool stats_pass = false) {
     case kExpWide: return shape_fn_mode<kExpWide>(s, stats_pass);
     case kExpFast: return shape_fn_mode<kExpFast>(s, stats_pass);
     case kLogOut: return shape_fn_mode<kLogOut>(s, stats_pass);
-    case kNllOut: return shape_fn_mode<kNllOut>(s, stats_pass);
+    case kNllOut: return s.kernel == SOFTMAX_KERNEL_PACKED ? packed_mode<kNllOut>(s) : nullptr;
     default: return shape_fn_mode<kExpAccurate>(s, stats_pass);
   }
 }
@@ -540,13 +546,13 @@ Shape default_shape(const float* x, const float* y, int64_t cols, int em) {
     s.kernel = SOFTMAX_KERNEL_WAVE_ROW;
     s.threads = 256;
     s.v = static_cast<int>(pow2_at_least(ceil_div(cols, 256)));
-  } else if (cols <= (em != kNllOut ? kSplitMinColsProb : kBlockRowMaxCols)) {
+  } else if (cols <= kSplitMinColsProb) {
     s.kernel = SOFTMAX_KERNEL_BLOCK_ROW;
     s.threads = kBlockThreads;
     s.v = static_cast<int>(std::max<int64_t>(2, pow2_at_least(ceil_div(cols, 4096))));
   } else {
     s.kernel = SOFTMAX_KERNEL_SPLIT_ROW;
-    if (em != kNllOut && ceil_div(cols, int64_t(4) * 8 * 256) <= kSmallChunkMaxChunks) {
+    if (ceil_div(cols, int64_t(4) * 8 * 256) <= kSmallChunkMaxChunks) {
       s.threads = 256;
       s.v = 8;
     } else if (ceil_div(cols, int64_t(4) * 8 * 512) <= kOnePassMaxChunks) {
@@ -579,7 +585,7 @@ bool requested_shape(const softmax_plan_t& want, const float* x, const float* y,
       s.kernel == SOFTMAX_KERNEL_WAVE_ROW || s.kernel == SOFTMAX_KERNEL_BLOCK_ROW;
   // The same for split rows (one pass, 8192- or 16384-column chunks).
   if (s.vec4 && s.kernel == SOFTMAX_KERNEL_SPLIT_ROW && split_phase_rows(x, y, cols) &&
-      em != kLogOut && em != kNllOut) {
+      em != kLogOut) {
     s.ph = true;
     s.threads = want.block_threads;
     s.v = want.elems_per_lane / 4;
@@ -589,7 +595,7 @@ bool requested_shape(const softmax_plan_t& want, const float* x, const float* y,
     *out = s;
     return true;
   }
-  if (s.vec4 && row_kernel && phase_rows(x, y, cols) && em != kLogOut && em != kNllOut) {
+  if (s.vec4 && row_kernel && phase_rows(x, y, cols) && em != kLogOut) {
     const int64_t span = cols + 3;
     if (span > (s.kernel == SOFTMAX_KERNEL_WAVE_ROW ? kWaveRowMaxCols : kSplitMinColsProb))
       return false;
@@ -611,7 +617,7 @@ bool requested_shape(const softmax_plan_t& want, const float* x, const float* y,
       s.v = 2;
       break;
     case SOFTMAX_KERNEL_PACKED:
-      if (cols > ((em == kLogOut || em == kNllOut) ? kPackedMaxCols : kPackedProbMaxCols))
+      if (cols > (em == kLogOut ? kPackedMaxCols : kPackedProbMaxCols))
         return false;
       s.threads = 256;
       s.g = packed_lanes(cols);
@@ -727,7 +733,7 @@ int library_shape(const float* x, const float* y, int64_t rows, int64_t cols, in
       s.epl = static_cast<int>(ceil_div(cols, s.g));
     }
   } else if (s.kernel == SOFTMAX_KERNEL_SPLIT_ROW && !s.two_pass && s.threads == 512 &&
-             s.v == 8 && em != kLogOut && em != kNllOut) {
+             s.v == 8 && em != kLogOut) {
     // Probability rows in 16384-column chunks: 8192-column chunks instead
     // by launches and grid fill (kSplitSparseNum, kSplitThinPerCU).
     Shape small = s;
@@ -756,7 +762,7 @@ int library_shape(const float* x, const float* y, int64_t rows, int64_t cols, in
       }
     }
   } else if (s.kernel == SOFTMAX_KERNEL_SPLIT_ROW && !s.two_pass && !s.ph && s.vec4 &&
-             s.threads == 256 && s.v == 8 && em != kLogOut && em != kNllOut &&
+             s.threads == 256 && s.v == 8 && em != kLogOut &&
              cols > 2 * chunk_cols(s) && cols < 3 * chunk_cols(s) &&
              rows * kBlockOverSplitMinRowsDen >= f.cus &&
              rows * kBlockOverSplitMaxRowsDen <= kBlockOverSplitMaxRowsNum * f.cus) {
@@ -823,7 +829,7 @@ int make_plan(const Shape& s, int64_t rows, int64_t cols, int em, int dev,
         p.launches = ceil_div(rows, p.rows_per_launch);
         // The store schedule pays with 128-bit access; with 32-bit access
         // (rows of 16383 and 32765 columns) it measured 0.1-0.4 us slower.
-        one_wave = em != kNllOut && s.vec4;
+        one_wave = s.vec4;
         launch_read_bytes = std::min(rows, p.rows_per_launch) * cols * 4;
       } else {
         // Workgroup w of a row takes chunks w, w + wpr, ...
@@ -885,16 +891,6 @@ softmax_plan_t public_plan(const Plan& p, int64_t rows) {
 // ---------------------------------------------------------------------------
 // Launches.
 
-// The output and labels of rows r0.. of a call: y advances by a row of
-// outputs, or by one loss per row for NLL outputs (whose labels advance
-// with it).
-inline float* out_rows(float* y, int64_t r0, int64_t cols, int em) {
-  return em == kNllOut ? y + r0 : y + r0 * cols;
-}
-inline const int64_t* label_rows(const int64_t* labels, int64_t r0, int em) {
-  return em == kNllOut ? labels + r0 : labels;
-}
-
 hipError_t run_plan(const Plan& p, const float* x, float* y, const int64_t* labels,
                     int64_t rows, int64_t cols, Clip c, int em, const DeviceFacts& f,
                     hipStream_t st) {
@@ -912,7 +908,7 @@ hipError_t run_plan(const Plan& p, const float* x, float* y, const int64_t* labe
     }
     case SOFTMAX_KERNEL_WAVE_ROW:
     case SOFTMAX_KERNEL_BLOCK_ROW: {
-      void* args[] = {&x, &y, &labels, &rows, &cols, &c, &delay};
+      void* args[] = {&x, &y, &rows, &cols, &c, &delay};
       return launch(fn, p.grid, s.threads, args, st);
     }
     default:
@@ -924,8 +920,7 @@ hipError_t run_plan(const Plan& p, const float* x, float* y, const int64_t* labe
     for (int64_t r0 = 0; r0 < rows; r0 += p.rows_per_launch) {
       const int64_t nb = std::min(p.rows_per_launch, rows - r0);
       const float* xb = x + r0 * cols;
-      float* yb = out_rows(y, r0, cols, em);
-      const int64_t* lb = label_rows(labels, r0, em);
+      float* yb = y + r0 * cols;
       // A short last launch waits only as long as its own reads take: with
       // the first launch's delay, 10 rows of 40000 columns after 409 waited
       // 8.9 us before storing.
@@ -935,7 +930,7 @@ hipError_t run_plan(const Plan& p, const float* x, float* y, const int64_t* labe
       }
       XchArgs xa{f.scratch, exchange_key(yb, nonce), p.limit_ticks, 1u,  // join
                  entry_base(f, nb), 0u};
-      void* args[] = {&xb, &yb, &lb, &xa, &cols, &ichunks, &delay, &c};
+      void* args[] = {&xb, &yb, &xa, &cols, &ichunks, &delay, &c};
       const hipError_t e = launch(fn, nb * p.chunks, s.threads, args, st);
       if (e != hipSuccess) return e;
     }
@@ -947,18 +942,143 @@ hipError_t run_plan(const Plan& p, const float* x, float* y, const int64_t* labe
   for (int64_t r0 = 0; r0 < rows; r0 += p.rows_per_launch) {
     const int64_t nb = std::min(p.rows_per_launch, rows - r0);
     const float* xb = x + r0 * cols;
-    float* yb = out_rows(y, r0, cols, em);
-    const int64_t* lb = label_rows(labels, r0, em);
+    float* yb = y + r0 * cols;
     XchArgs xa{f.scratch, exchange_key(yb, nonce), p.limit_ticks, 1u, entry_base(f, nb), 0u};
     void* a1[] = {&xb, &xa, &cols, &iwpr, &chunks, &c};
     hipError_t e = launch(fn_stats, nb * p.wpr, s.threads, a1, st);
     if (e != hipSuccess) return e;
     XchArgs xb2{f.scratch, xa.key, p.limit_ticks, 0u, xa.base, 0u};  // find only
-    void* a2[] = {&xb, &yb, &lb, &xb2, &cols, &iwpr, &chunks, &c};
+    void* a2[] = {&xb, &yb, &xb2, &cols, &iwpr, &chunks, &c};
     e = launch(fn, nb * p.wpr, s.threads, a2, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+// ---------------------------------------------------------------------------
+// NLL rows of more than kPackedMaxCols columns (sm_nll.hpp).
+
+// k_nll_group takes rows of up to kNllGroupMaxStrips aligned strips: G lanes
+// per row so that a lane holds 3 to 8 of them.  The line between two G was
+// measured per 64 MiB: 200 columns (51 strips) 13.2 us with G = 8 and 13.5
+// with 16; 255 and 360 columns 13.0 and 12.9 with 16 against 13.8 and 13.3
+// with 32; 520 and 777 columns 12.9 with 32 against 14.5 and 13.3 with 64;
+// 1000 columns 12.6 with 64 against 13.2 with 32.
+constexpr int64_t kNllGroup8Strips = 56;
+constexpr int64_t kNllGroup16Strips = 96;
+constexpr int64_t kNllGroup32Strips = 200;
+constexpr int64_t kNllGroupMaxStrips = 512;
+// Longer rows: one wavefront per row, or 256 threads from kNllMidCols
+// columns (1677 x 10000 level, 2795 x 6001 13.2 against 12.7 us), and more
+// while the rows would keep fewer than kNllMinThreadsPerCU (short rows:
+// kNllMinThreadsPerCUShort) threads per CU busy: 349 x 6001 ran 4.6 us with 512 threads per row, 4.9 with 256 and 6.6
+// with 64; 209 x 10000 4.65 with 1024 and 4.9 with 512; 128 x 40000 7.3 with 1024 against 7.6 with 512; but 400 x 65539
+// 18.5 with 256 and 20.1 with 512 or 1024.  Long rows that fill the device
+// four times over take 1024 threads: 4096 x 50001 ran 125.5 us, against
+// 129.8 with 512 and 133.7 with 256.
+constexpr int64_t kNllMidCols = 8192;
+constexpr int64_t kNllMinThreadsPerCU = 384;
+constexpr int64_t kNllMinThreadsPerCUShort = 512;
+constexpr int64_t kNllShortCols = 16384;
+constexpr int64_t kNllLongCols = 32768;
+constexpr int64_t kNllManyRowsPerCU = 4;
+// Up to half as many rows as CUs: rows of more than kNllSplitCols +
+// kNllSplitColsPerRow * rows columns are split over workgroups of 512
+// threads, so that about four per CU share the launch's bytes in chunks of
+// at least kNllSplitMinChunk columns.  Measured split against the best single
+// workgroup per row: 64 x 262144 14.6 us (unsplit 20 and more), 30 x 50001
+// 6.4 against 7.0, 20 x 30003 5.6 and 5.6, 64 x 32768 6.3 against 5.3,
+// 100 x 50001 8.9 against 8.5, 200 x 131072 20.3 against 18.9.
+constexpr int64_t kNllSplitCols = 32768;
+constexpr int64_t kNllSplitColsPerRow = 200;
+constexpr int64_t kNllSplitMinChunk = 8192;
+constexpr int64_t kNllSplitWorkgroupsPerCU = 4;
+constexpr int kNllStrips = 4;  // strips per lane and step of a streamed row
+
+const void* nll_group_fn(int64_t strips, int* lanes) {
+  auto cast = [](auto f) { return reinterpret_cast<const void*>(f); };
+  if (strips <= kNllGroup8Strips) {
+    *lanes = 8;
+    switch (ceil_div(strips, 8)) {
+      case 4: return cast(&k_nll_group<8, 4>);
+      case 5: return cast(&k_nll_group<8, 5>);
+      case 6: return cast(&k_nll_group<8, 6>);
+      case 7: return cast(&k_nll_group<8, 7>);
+      default: return cast(&k_nll_group<8, 3>);
+    }
+  }
+  if (strips <= kNllGroup16Strips) {
+    *lanes = 16;
+    switch (ceil_div(strips, 16)) {
+      case 4: return cast(&k_nll_group<16, 4>);
+      case 5: return cast(&k_nll_group<16, 5>);
+      default: return cast(&k_nll_group<16, 6>);
+    }
+  }
+  if (strips <= kNllGroup32Strips) {
+    *lanes = 32;
+    switch (ceil_div(strips, 32)) {
+      case 4: return cast(&k_nll_group<32, 4>);
+      case 5: return cast(&k_nll_group<32, 5>);
+      case 6: return cast(&k_nll_group<32, 6>);
+      default: return cast(&k_nll_group<32, 7>);
+    }
+  }
+  *lanes = 64;
+  switch (ceil_div(strips, 64)) {
+    case 4: return cast(&k_nll_group<64, 4>);
+    case 5: return cast(&k_nll_group<64, 5>);
+    case 6: return cast(&k_nll_group<64, 6>);
+    case 7: return cast(&k_nll_group<64, 7>);
+    default: return cast(&k_nll_group<64, 8>);
+  }
+}
+
+const void* nll_rows_fn(int threads) {
+  switch (threads) {
+    case 64: return reinterpret_cast<const void*>(&k_nll_rows<64, kNllStrips>);
+    case 256: return reinterpret_cast<const void*>(&k_nll_rows<256, kNllStrips>);
+    case 512: return reinterpret_cast<const void*>(&k_nll_rows<512, kNllStrips>);
+    default: return reinterpret_cast<const void*>(&k_nll_rows<1024, kNllStrips>);
+  }
+}
+
+// Threads per unsplit row.
+int nll_threads(int64_t rows, int64_t cols, const DeviceFacts& f) {
+  if (cols >= kNllLongCols && rows >= kNllManyRowsPerCU * f.cus) return 1024;
+  int nt = cols < kNllMidCols ? 64 : 256;
+  const int64_t busy =
+      f.cus * (cols < kNllShortCols ? kNllMinThreadsPerCUShort : kNllMinThreadsPerCU);
+  while (nt < 1024 && rows * nt < busy && int64_t(8) * nt <= cols)
+    nt = nt == 64 ? 256 : 2 * nt;
+  return nt;
+}
+
+hipError_t run_nll(const float* x, float* y, const int64_t* labels, int64_t rows, int64_t cols,
+                   Clip c, const DeviceFacts& f, hipStream_t st) {
+  void* args[] = {&x, &labels, &y, &rows, &cols, &c};
+  const int64_t strips = aligned16(x) && cols % 4 == 0 ? cols / 4 : ceil_div(cols + 3, 4);
+  if (strips <= kNllGroupMaxStrips) {
+    int lanes = 0;
+    const void* fn = nll_group_fn(strips, &lanes);
+    return launch(fn, std::min(ceil_div(rows, 4 * (64 / lanes)), kMaxGrid), 256, args, st);
+  }
+  if (2 * rows > f.cus || cols <= kNllSplitCols + kNllSplitColsPerRow * rows) {
+    const int nt = nll_threads(rows, cols, f);
+    return nt == 64 ? launch(nll_rows_fn(nt), std::min(ceil_div(rows, 4), kMaxGrid), 256, args, st)
+                    : launch(nll_rows_fn(nt), std::min(rows, kMaxGrid), nt, args, st);
+  }
+  // At most CUs / 2 rows, each of at least five chunks: one launch.
+  const int64_t want = std::min({int64_t(xch::kEntrySlots),
+                                 ceil_div(kNllSplitWorkgroupsPerCU * f.cus, rows),
+                                 ceil_div(cols, kNllSplitMinChunk)});
+  int64_t chunk = (ceil_div(cols, want) + 3) & ~int64_t(3);
+  int chunks = static_cast<int>(ceil_div(cols, chunk));
+  XchArgs xa{f.scratch, exchange_key(y, g_nonce.fetch_add(1, std::memory_order_relaxed)),
+             ns_to_ticks(int64_t(xch::kWaitLimitUs) * 1000, f), 1u, entry_base(f, rows), 0u};
+  void* split_args[] = {&x, &labels, &y, &xa, &cols, &chunks, &chunk, &c};
+  return launch(reinterpret_cast<const void*>(&k_nll_split<512, kNllStrips>), rows * chunks, 512,
+                split_args, st);
 }
 
 int check_pointers(const float* x, const float* y, int64_t n_elems, int* dev) {
@@ -1106,11 +1226,15 @@ SOFTMAX_API int softmax_nll_fwd(const float* x, const int64_t* labels, float* lo
   if ((rc = check_device_range(loss, obytes, dev)) != SOFTMAX_OK) return rc;
   DeviceFacts f;
   if ((rc = device_facts(dev, &f)) != SOFTMAX_OK) return rc;
-  // The access width follows x alone: the losses are 32-bit stores.
-  Plan p;
-  rc = make_plan(default_shape(x, x, cols, kNllOut), rows, cols, kNllOut, dev, f, -1, &p);
-  if (rc != SOFTMAX_OK) return rc;
-  e = run_plan(p, x, loss, labels, rows, cols, c, kNllOut, f, stream);
+  if (cols <= kPackedMaxCols) {
+    // The access width follows x alone: the losses are 32-bit stores.
+    Plan p;
+    rc = make_plan(default_shape(x, x, cols, kNllOut), rows, cols, kNllOut, dev, f, -1, &p);
+    if (rc != SOFTMAX_OK) return rc;
+    e = run_plan(p, x, loss, labels, rows, cols, c, kNllOut, f, stream);
+  } else {
+    e = run_nll(x, loss, labels, rows, cols, c, f, stream);
+  }
   return e == hipSuccess ? SOFTMAX_OK : fail_hip(e);
 }
 
