@@ -3,20 +3,18 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 
 #include "../../include/softmax_mi355x.h"
 #include "sm_attention.hpp"
+#include "sm_attention_wave.hpp"
 #include "sm_host.hpp"
 
 namespace {
 
 using namespace smx;
 using namespace smx_host;
-
-// Workgroups per CU for the persistent grid (each holds 4 wavefronts of one
-// batch element's 64-query block at a time).
-constexpr int64_t kAttnBlocksPerCU = 8;
 
 // sizes: all >= 0, lk in [1, 64] when there is work, d and dv at most
 // SOFTMAX_ATTN_MAX_DIM, and every tensor's byte count fits in int64.
@@ -31,30 +29,6 @@ int check_attention_sizes(int64_t batch, int64_t lq, int64_t lk, int64_t d, int6
   const int64_t per_k = lk * std::max<int64_t>(d, dv);
   if (batch > INT64_MAX / 4 / std::max(per_q, per_k)) return SOFTMAX_ERR_INVALID_ARG;
   return SOFTMAX_OK;
-}
-
-template <int NKT, bool VEC4, bool WIDE>
-hipError_t run_attention(const float* q, const float* k, const float* v, float* o,
-                         int64_t batch, int lq, int lk, int d, int dv, float scale, Clip c,
-                         int64_t cus, hipStream_t s) {
-  const int64_t items = batch * ((lq + 63) / 64);
-  const int64_t grid = std::min(items, kAttnBlocksPerCU * cus);
-  void* args[] = {&q, &k, &v, &o, &batch, &lq, &lk, &d, &dv, &scale, &c};
-  return launch(reinterpret_cast<const void*>(&k_attention<NKT, VEC4, WIDE>), grid, 256, args,
-                s);
-}
-
-// LDS-staged kernel: two workgroups per CU (80 KiB of LDS each).
-constexpr int64_t kAttnLdsBlocksPerCU = 2;
-
-template <int NKT, bool WIDE>
-hipError_t run_attention_lds(const float* q, const float* k, const float* v, float* o,
-                             int64_t batch, int lq, int lk, int d, int dv, float scale, Clip c,
-                             int64_t cus, hipStream_t s) {
-  const int64_t items = batch * ((lq + 63) / 64);
-  const int64_t grid = std::min(items, kAttnLdsBlocksPerCU * cus);
-  void* args[] = {&q, &k, &v, &o, &batch, &lq, &lk, &d, &dv, &scale, &c};
-  return launch(reinterpret_cast<const void*>(&k_attention_lds<NKT, WIDE>), grid, 256, args, s);
 }
 
 // The DAM tile (d = dv = 200, 49 or 50 keys) with d known at compile time,
@@ -79,28 +53,88 @@ hipError_t run_attention_dam(const float* q, const float* k, const float* v, flo
                 args, s);
 }
 
-template <bool WIDE>
-hipError_t dispatch_attention_lds(const float* q, const float* k, const float* v, float* o,
-                                  int64_t batch, int lq, int lk, int d, int dv, float scale,
-                                  Clip c, int64_t cus, hipStream_t s) {
-  switch ((lk + 15) / 16) {
-    case 1: return run_attention_lds<1, WIDE>(q, k, v, o, batch, lq, lk, d, dv, scale, c, cus, s);
-    case 2: return run_attention_lds<2, WIDE>(q, k, v, o, batch, lq, lk, d, dv, scale, c, cus, s);
-    case 3: return run_attention_lds<3, WIDE>(q, k, v, o, batch, lq, lk, d, dv, scale, c, cus, s);
-    default: return run_attention_lds<4, WIDE>(q, k, v, o, batch, lq, lk, d, dv, scale, c, cus, s);
+// ---------------------------------------------------------------------------
+// One wavefront per block of queries (sm_attention_wave.hpp): everything but
+// the DAM tile.
+
+// Instances: NQ x NK x access (rows of whole 128-byte lines read once: nt
+// loads; other rows of whole 16-byte strips; other rows).
+enum WaveAccess { kWaveStream, kWaveWhole, kWaveRagged };
+
+template <int NQ, bool RAGGED, bool STREAM>
+const void* wave_fn_nk(int nk) {
+  auto cast = [](auto f) { return reinterpret_cast<const void*>(f); };
+  switch (nk) {
+    case 1: return cast(&k_attention_wave<NQ, 1, RAGGED, STREAM>);
+    case 2: return cast(&k_attention_wave<NQ, 2, RAGGED, STREAM>);
+    case 3: return cast(&k_attention_wave<NQ, 3, RAGGED, STREAM>);
+    default: return cast(&k_attention_wave<NQ, 4, RAGGED, STREAM>);
   }
 }
 
-template <bool VEC4, bool WIDE>
-hipError_t dispatch_attention(const float* q, const float* k, const float* v, float* o,
-                              int64_t batch, int lq, int lk, int d, int dv, float scale,
-                              Clip c, int64_t cus, hipStream_t s) {
-  switch ((lk + 15) / 16) {
-    case 1: return run_attention<1, VEC4, WIDE>(q, k, v, o, batch, lq, lk, d, dv, scale, c, cus, s);
-    case 2: return run_attention<2, VEC4, WIDE>(q, k, v, o, batch, lq, lk, d, dv, scale, c, cus, s);
-    case 3: return run_attention<3, VEC4, WIDE>(q, k, v, o, batch, lq, lk, d, dv, scale, c, cus, s);
-    default: return run_attention<4, VEC4, WIDE>(q, k, v, o, batch, lq, lk, d, dv, scale, c, cus, s);
+template <bool RAGGED, bool STREAM>
+const void* wave_fn(int nq, int nk) {
+  switch (nq) {
+    case 1: return wave_fn_nk<1, RAGGED, STREAM>(nk);
+    case 2: return wave_fn_nk<2, RAGGED, STREAM>(nk);
+    default: return wave_fn_nk<3, RAGGED, STREAM>(nk);
   }
+}
+
+// Query tiles per wavefront: two (each K and V operand serves two matrix
+// ops), or three for 33 to 48 queries, where two would leave one of four tiles
+// empty (4096 x 33 x 37 x 50 x 50 33 us against 43).  Four tiles measured
+// level on 64 queries at 8192 items and 2-30% slower below (1024 x 64 x 64 x
+// 64 x 64 20.2 us against 16.9).  Fewer while that would leave fewer than
+// kAttnMinWavesPerCU wavefronts per CU: 256 x 64 x 64 x 64 x 64 ran 7.6 us
+// with one tile (1024 wavefronts) and 10.2 with two (512).
+constexpr int64_t kAttnMinWavesPerCU = 4;
+
+// Resident workgroups per CU of an instance, from the runtime's occupancy
+// calculator (the same on every gfx950 device), once per instance.
+std::atomic<int> g_wave_per_cu[3][4][3][2];
+
+int wave_per_cu(const void* fn, int nq, int nk, WaveAccess access, int waves, int* out) {
+  std::atomic<int>& slot = g_wave_per_cu[nq - 1][nk - 1][access][waves > 1];
+  int n = slot.load(std::memory_order_relaxed);
+  if (n == 0) {
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, 64 * waves, 0);
+    if (e != hipSuccess) return fail_hip(e);
+    if (n <= 0) return SOFTMAX_ERR_HIP;
+    slot.store(n, std::memory_order_relaxed);
+  }
+  *out = n;
+  return SOFTMAX_OK;
+}
+
+int run_attention_wave(const float* q, const float* k, const float* v, float* o, int64_t batch,
+                       int lq, int lk, int d, int dv, float scale, Clip c, int64_t cus,
+                       hipStream_t s) {
+  auto blocks = [&](int n) { return batch * ((lq + 16 * n - 1) / (16 * n)); };
+  const int tiles = (lq + 15) / 16;
+  int nq = tiles == 3 ? 3 : std::min(tiles, 2);
+  while (nq > 1 && blocks(nq) < kAttnMinWavesPerCU * cus) --nq;
+  const int nk = (lk + 15) / 16;
+  const int64_t items = blocks(nq);
+  const WaveAccess access = d % 4 != 0 ? kWaveRagged
+                            : items == batch && d % 32 == 0 && dv % 32 == 0 ? kWaveStream
+                                                                            : kWaveWhole;
+  const void* fn = access == kWaveRagged   ? wave_fn<true, false>(nq, nk)
+                   : access == kWaveStream ? wave_fn<false, true>(nq, nk)
+                                           : wave_fn<false, false>(nq, nk);
+  // Four wavefronts per workgroup share a batch element's K and V through
+  // their CU's cache; at most one item per CU takes a CU each (100 x 16 x 50 x
+  // 200 x 200 ran 13.4 us so, 17.8 on 25 CUs).
+  const int waves = items <= cus ? 1 : 4;
+  int per_cu = 0;
+  const int rc = wave_per_cu(fn, nq, nk, access, waves, &per_cu);
+  if (rc != SOFTMAX_OK) return rc;
+  // Resident workgroups only, each looping over items: the next item's first
+  // operands load during this one's softmax and value product.
+  const int64_t grid = std::min(ceil_div(items, waves), int64_t(per_cu) * cus);
+  void* args[] = {&q, &k, &v, &o, &batch, &lq, &lk, &d, &dv, &scale, &c};
+  const hipError_t e = launch(fn, grid, 64 * waves, args, s);
+  return e == hipSuccess ? SOFTMAX_OK : fail_hip(e);
 }
 
 }  // namespace
@@ -146,33 +180,22 @@ SOFTMAX_API int softmax_attention_fwd(const float* q, const float* k, const floa
 
   int cus = 0;
   if ((rc = device_cus(dev, &cus)) != SOFTMAX_OK) return rc;
-  // 128-bit accesses for every operand, or 32-bit ones for all of them.
+  // 16-byte aligned rows throughout (the DAM tile's LDS copies).
   const bool vec4 = d % 4 == 0 && dv % 4 == 0 && aligned16(q) && aligned16(k) &&
                     aligned16(v) && aligned16(o);
   const int ilq = static_cast<int>(lq), ilk = static_cast<int>(lk);
   const int id = static_cast<int>(d), idv = static_cast<int>(dv);
-  // K_b and V_b staged in LDS when they fit and every access is 128-bit.
-  const bool lds = vec4 && d <= kAttnMaxDQ && lk * (d + dv) * 4 <= kAttnLdsBytes;
-  if (lds && dam_tile(ilk, id, idv))
+  // The DAM tile runs 64-query items on the ping-pong kernel, one per CU and
+  // turn; many items of one query tile fill a quarter of it and run faster a
+  // wavefront each (2000 x 16 x 50 x 200 x 200 45 us against 61, 2000 x 1
+  // 35 against 59; 2000 x 32 level; 100 x 16 13.4 against 10.0).
+  if (vec4 && dam_tile(ilk, id, idv) && (lq > 16 || batch < kAttnMinWavesPerCU * cus)) {
     e = wide ? run_attention_dam<true>(q, k, v, o, batch, ilq, ilk, id, idv, scale, c, cus, stream)
              : run_attention_dam<false>(q, k, v, o, batch, ilq, ilk, id, idv, scale, c, cus,
                                         stream);
-  else if (lds)
-    e = wide ? dispatch_attention_lds<true>(q, k, v, o, batch, ilq, ilk, id, idv, scale, c,
-                                            cus, stream)
-             : dispatch_attention_lds<false>(q, k, v, o, batch, ilq, ilk, id, idv, scale, c,
-                                             cus, stream);
-  else if (vec4)
-    e = wide ? dispatch_attention<true, true>(q, k, v, o, batch, ilq, ilk, id, idv, scale, c,
-                                              cus, stream)
-             : dispatch_attention<true, false>(q, k, v, o, batch, ilq, ilk, id, idv, scale, c,
-                                               cus, stream);
-  else
-    e = wide ? dispatch_attention<false, true>(q, k, v, o, batch, ilq, ilk, id, idv, scale, c,
-                                               cus, stream)
-             : dispatch_attention<false, false>(q, k, v, o, batch, ilq, ilk, id, idv, scale, c,
-                                                cus, stream);
-  return e == hipSuccess ? SOFTMAX_OK : fail_hip(e);
+    return e == hipSuccess ? SOFTMAX_OK : fail_hip(e);
+  }
+  return run_attention_wave(q, k, v, o, batch, ilq, ilk, id, idv, scale, c, cus, stream);
 }
 
 }  // extern "C"

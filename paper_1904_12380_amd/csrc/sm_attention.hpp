@@ -14,9 +14,8 @@
 // A[i][k] in lane i + 16k, B[k][j] in lane j + 16k, and C[i][j] in lane
 // j + 16 (i / 4), register i % 4):
 //
-//   * A workgroup of 4 wavefronts takes one batch element and a block of up
-//     to 64 queries; wavefront w takes queries 16w .. 16w+15 of the block.
-//     Write lane = j + 16 g (j = lane % 16, g = lane / 16).
+//   * A wavefront takes 16 queries at a time (here 4 wavefronts a block of up
+//     to 64; sm_attention_wave.hpp: one wavefront 16, 32 or 48).  Write lane = j + 16 g (j = lane % 16, g = lane / 16).
 //   * Scores, transposed: S^T[key][query] = sum_t K[key][t] Q[query][t],
 //     for NKT key tiles of 16.  The contraction index runs over d in blocks
 //     of 16; within a block, lane g of step s holds t = 16 blk + 4 g + s, so
@@ -86,199 +85,9 @@ __device__ __forceinline__ f32x4m buf_load4(__amdgpu_buffer_rsrc_t r, int off, b
   }
 }
 
-template <int NKT, bool VEC4, bool WIDE>
-__global__ __launch_bounds__(256) void k_attention(const float* q, const float* k,
-                                                   const float* v, float* o, int64_t batch,
-                                                   int lq, int lk, int d, int dv, float scale,
-                                                   Clip clip) {
-  const int lane = __lane_id();
-  const int j = lane & 15;
-  const int g = lane >> 4;
-  // The wave index is uniform across the wave; saying so keeps the buffer
-  // resources built from it in scalar registers.
-  const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
-  const int qblocks = (lq + 63) >> 6;
-  const int64_t items = batch * qblocks;
-
-  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
-    const int64_t b = item / qblocks;
-    const int q0 = static_cast<int>(item - b * qblocks) * 64 + 16 * w;  // this wave's queries
-    if (q0 >= lq) continue;                       // wave-uniform; no barriers below
-    const int nq = lq - q0 < 16 ? lq - q0 : 16;   // valid queries of this wave
-    // The wave's 16 query rows of Q and O, and the batch element's K and V.
-    const __amdgpu_buffer_rsrc_t rq =
-        make_rsrc(q + (b * lq + q0) * static_cast<int64_t>(d), nq * d * 4);
-    const __amdgpu_buffer_rsrc_t rk = make_rsrc(k + b * lk * static_cast<int64_t>(d), lk * d * 4);
-    const __amdgpu_buffer_rsrc_t rv = make_rsrc(v + b * lk * static_cast<int64_t>(dv), lk * dv * 4);
-    const __amdgpu_buffer_rsrc_t ro =
-        make_rsrc(o + (b * lq + q0) * static_cast<int64_t>(dv), nq * dv * 4);
-
-    // ---- scores S^T = K Q^T for this wave's 16 queries --------------------
-    // Lane (j, g) reads query j and key 16 kt + j at columns t0 .. t0+3,
-    // t0 = 16 blk + 4 g; columns past d (last block only) read as zero.
-    const int qoff = (j * d + 4 * g) * 4;
-    const int koff = (j * d + 4 * g) * 4;
-    const int kstride = 16 * d * 4;               // one key tile
-    f32x4m acc[NKT];
-#pragma unroll
-    for (int kt = 0; kt < NKT; ++kt) acc[kt] = f32x4m{0.0f, 0.0f, 0.0f, 0.0f};
-    const int nblk = (d + 15) >> 4;               // uniform trip count for the matrix ops
-    if (nblk > 0) {
-      // Operands of blocks blk, blk+1 are in registers while block blk+2 is
-      // loaded: two blocks of loads stay in flight behind the matrix ops.
-      const int left0 = d - 4 * g, left1 = d - 16 - 4 * g;
-      f32x4m qf0 = buf_load4<VEC4>(rq, qoff, left0 > 0, left0);
-      f32x4m qf1 = buf_load4<VEC4>(rq, qoff + 64, (nblk > 1) & (left1 > 0), left1);
-      f32x4m kf0[NKT], kf1[NKT];
-#pragma unroll
-      for (int kt = 0; kt < NKT; ++kt) {
-        kf0[kt] = buf_load4<VEC4>(rk, koff + kt * kstride, left0 > 0, left0);
-        kf1[kt] = buf_load4<VEC4>(rk, koff + kt * kstride + 64, (nblk > 1) & (left1 > 0), left1);
-      }
-      for (int blk = 0; blk < nblk; ++blk) {
-        const int left = d - 16 * (blk + 2) - 4 * g;
-        const bool more = (blk + 2 < nblk) & (left > 0);
-        const int step = 64 * (blk + 2);
-        const f32x4m qn = buf_load4<VEC4>(rq, qoff + step, more, left);
-        f32x4m kn[NKT];
-#pragma unroll
-        for (int kt = 0; kt < NKT; ++kt)
-          kn[kt] = buf_load4<VEC4>(rk, koff + kt * kstride + step, more, left);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-#pragma unroll
-          for (int kt = 0; kt < NKT; ++kt) acc[kt] = mfma16x16x4(kf0[kt][s], qf0[s], acc[kt]);
-        }
-        qf0 = qf1;
-        qf1 = qn;
-#pragma unroll
-        for (int kt = 0; kt < NKT; ++kt) {
-          kf0[kt] = kf1[kt];
-          kf1[kt] = kn[kt];
-        }
-      }
-    }
-
-    // ---- clipped softmax over the keys of query j -------------------------
-    // Only the last key tile can hold keys past lk (NKT = ceil(lk / 16)).
-    float e[4 * NKT];
-    float m = -__builtin_inff();
-#pragma unroll
-    for (int kt = 0; kt < NKT; ++kt) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const bool key_ok = kt < NKT - 1 || 16 * kt + 4 * g + r < lk;
-        const float sv = acc[kt][r] * scale;
-        e[4 * kt + r] = sv;
-        m = key_ok ? fmaxf(m, sv) : m;
-      }
-    }
-    m = fmaxf(m, row16_partner(m));
-    m = fmaxf(m, half32_partner(m));
-    const RowShift rs = row_shift(m, clip);
-#pragma unroll
-    for (int kt = 0; kt < NKT; ++kt) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const bool key_ok = kt < NKT - 1 || 16 * kt + 4 * g + r < lk;
-        const float ev = exp_shift_clip<WIDE ? kExpWide : kExpAccurate>(e[4 * kt + r], rs);
-        e[4 * kt + r] = key_ok ? ev : 0.0f;
-      }
-    }
-    float sum = tree_sum(e);
-    sum = sum + row16_partner(sum);
-    sum = sum + half32_partner(sum);
-    const float rcp = 1.0f / sum;
-#pragma unroll
-    for (int i = 0; i < 4 * NKT; ++i) e[i] = e[i] * rcp;
-
-    // ---- O = P V ----------------------------------------------------------
-    // Contraction step i = 4 kt + r takes key 16 kt + 4 g + r in lane
-    // (j, g): byte offset vlane + i' * dv * 4 with i' = 16 kt + r.  Keys past
-    // lk fall outside the resource and read as zero.
-    const int vlane = 4 * g * dv * 4;
-    const int orow = 4 * g * dv * 4;              // O row 4 g + r of the wave
-    // Full 64-column blocks with 128-bit access (VEC4): lane j takes
-    // columns c0 + 4 j .. c0 + 4 j + 3, one per column tile u, so a lane's
-    // four tiles are one 128-bit load of V and one 128-bit store of O.  The
-    // block is done in two halves of 2 NKT contraction steps; the next
-    // half's loads are in flight while this half's matrix ops run.
-    constexpr int H = 2 * NKT;
-    const int nfull = VEC4 ? dv >> 6 : 0;
-    if (nfull > 0) {
-      f32x4m va[H], vh[H];
-#pragma unroll
-      for (int i = 0; i < H; ++i)
-        va[i] = buf_load4<true>(rv, vlane + ((16 * (i >> 2) + (i & 3)) * dv + 4 * j) * 4, true);
-      for (int cb = 0; cb < nfull; ++cb) {
-        const int c = 64 * cb + 4 * j;
-#pragma unroll
-        for (int i = 0; i < H; ++i) {
-          const int ii = H + i;
-          vh[i] = buf_load4<true>(rv, vlane + ((16 * (ii >> 2) + (ii & 3)) * dv + c) * 4, true);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        f32x4m oacc[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) oacc[u] = f32x4m{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int i = 0; i < H; ++i) {
-#pragma unroll
-          for (int u = 0; u < 4; ++u) oacc[u] = mfma16x16x4(e[i], va[i][u], oacc[u]);
-        }
-        const bool next = cb + 1 < nfull;
-#pragma unroll
-        for (int i = 0; i < H; ++i)
-          va[i] = buf_load4<true>(rv, vlane + ((16 * (i >> 2) + (i & 3)) * dv + c + 64) * 4, next);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < H; ++i) {
-#pragma unroll
-          for (int u = 0; u < 4; ++u) oacc[u] = mfma16x16x4(e[H + i], vh[i][u], oacc[u]);
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const f32x4m ov = {oacc[0][r], oacc[1][r], oacc[2][r], oacc[3][r]};
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(
-              __attribute__((ext_vector_type(4))) unsigned, ov), ro, orow + (r * dv + c) * 4, 0, 0);
-        }
-      }
-    }
-    // The remaining columns (all of them without 128-bit access), one plain
-    // 16-column tile at a time: lane j takes column c0 + j.  Columns past dv
-    // would land in the next row, so their loads use an offset past the
-    // resource, and their stores are skipped.
-    for (int c0 = 64 * nfull; c0 < dv; c0 += 16) {
-      const int c = c0 + j;
-      const bool c_ok = c < dv;
-      float vs[4 * NKT];
-#pragma unroll
-      for (int i = 0; i < 4 * NKT; ++i) {
-        const int off = c_ok ? vlane + ((16 * (i >> 2) + (i & 3)) * dv + c) * 4 : kBufOff;
-        vs[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rv, off, 0, 0));
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      f32x4m oa = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int i = 0; i < 4 * NKT; ++i) oa = mfma16x16x4(e[i], vs[i], oa);
-      // Plain stores here: a 32-bit buffer store of an accumulator element
-      // was compiled to store element 0 for every r by this toolchain.
-      float* orow_p = o + (b * lq + q0 + 4 * g) * static_cast<int64_t>(dv) + c;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if ((q0 + 4 * g + r < lq) & c_ok)
-          __builtin_nontemporal_store(oa[r], orow_p + static_cast<int64_t>(r) * dv);
-      }
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------
-// The same computation with K_b and V_b staged in LDS, for problems whose
-// lk * (d + dv) floats fit in kAttnLdsBytes and whose rows allow 128-bit
-// access (d % 4 == dv % 4 == 0, 16-byte aligned operands).  Four wavefronts
-// take one batch element (and one block of 64 queries):
+// The DAM tile (d = dv = DC known at compile time) with K_b and V_b staged in
+// LDS.  Four wavefronts take one batch element (and one block of 64 queries):
 //
 //   1. the 4 wavefronts copy K_b and V_b, which are contiguous, into LDS
 //      with LDS-DMA loads (global_load_lds_dwordx4: 1 KiB per wavefront
@@ -288,20 +97,13 @@ __global__ __launch_bounds__(256) void k_attention(const float* q, const float* 
 //      registers as before, and the P.V product reads V from LDS;
 //   3. a barrier ends the item before the next one overwrites the LDS.
 //
-// Each batch element's K and V cross HBM and L2 once, instead of once per
-// wavefront, and the matrix-op operands come from LDS.  Two schedules:
-//
-//   * k_attention_lds: two workgroups of 4 wavefronts per CU, each with its
-//     own 80 KiB of LDS, one item after another (copy, wait, compute).  The
-//     two do not stay out of step, so copies and matrix ops overlap only
-//     in part.
-//   * k_attention_pp: one workgroup of 8 wavefronts per CU in two teams that
-//     take turns: one computes an item while the other copies the next.
-//     Used with d = dv = DC known at compile time (the DAM tile, DC = 200),
-//     where the masks and branches of the d loops fold away, the matrix ops
-//     issue back to back, and the last key tile (at most 2 keys) is scored
-//     on the VALU; with d at run time one wavefront per SIMD computes too
-//     slowly for this schedule.
+// Each batch element's K and V cross HBM and L2 once.  k_attention_pp runs
+// one workgroup of 8 wavefronts per CU in two teams that take turns: one
+// computes an item while the other copies the next.  With DC known the masks
+// and branches of the d loops fold away, the matrix ops issue back to back,
+// and the last key tile (at most 2 keys) is scored on the VALU.  Other shapes
+// take one wavefront per block of queries (sm_attention_wave.hpp; on the DAM
+// workload that runs 107 us against 79 here).
 constexpr int kAttnLdsBytes = 80 * 1024;  // one batch element's K_b and V_b
 constexpr int kAttnMaxDQ = 224;           // d up to this keeps Q in registers
 constexpr int kAttnQB = kAttnMaxDQ / 16;  // 16-wide blocks of d in registers
@@ -346,7 +148,7 @@ __device__ __forceinline__ void attn_load_q(f32x4m (&qf)[kAttnQB], const float* 
 #pragma unroll
   for (int blk = 0; blk < kAttnQB; ++blk) {
     // With d known at compile time a block wholly inside d needs no mask.
-    const bool in_d = (DC != 0 && 16 * blk + 16 <= d) || 16 * blk + 4 * g < d;
+    const bool in_d = (16 * blk + 16 <= d) || 16 * blk + 4 * g < d;
     qf[blk] = buf_load4<true>(rq, qoff + 64 * blk, (blk < nblk) & in_d);
   }
 }
@@ -456,117 +258,10 @@ __device__ __forceinline__ void attn_pv_stream(const float (&sc)[4 * NKT], const
   }
 }
 
-// The weights and the value product for d at run time (DC = 0): e holds
-// the scaled scores as in attn_pv_stream and becomes the normalised weights
-// before the product.
-template <int NKT, bool WIDE>
-__device__ __forceinline__ void attn_pv_rows(float (&e)[4 * NKT], const RowShift& rs,
-                                             const float* lv_s, float* o, int64_t b, int q0,
-                                             int nq, int lq, int lk, int dv, int j, int g) {
-#pragma unroll
-  for (int kt = 0; kt < NKT; ++kt) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const bool key_ok = kt < NKT - 1 || 16 * kt + 4 * g + r < lk;
-      const float ev = exp_shift_clip<WIDE ? kExpWide : kExpAccurate>(e[4 * kt + r], rs);
-      e[4 * kt + r] = key_ok ? ev : 0.0f;
-    }
-  }
-  float sum = tree_sum(e);
-  sum = sum + row16_partner(sum);
-  sum = sum + half32_partner(sum);
-  const float rcp = 1.0f / sum;
-#pragma unroll
-  for (int i = 0; i < 4 * NKT; ++i) e[i] = e[i] * rcp;
-
-  // ---- O = P V, V from LDS --------------------------------------------------
-  // Contraction step i = 4 kt + r: key 16 kt + 4 g + r.  Keys past lk (only
-  // in the last key tile) have weight 0; their value operand is row 0 zeroed
-  // at use, since a stale value could be NaN.
-  auto v_ok = [&](int i) { return (i >> 2) < NKT - 1 || 16 * (i >> 2) + 4 * g + (i & 3) < lk; };
-  auto vrow = [&](int i) { return (v_ok(i) ? 16 * (i >> 2) + 4 * g + (i & 3) : 0) * dv; };
-  // A step whose smallest key (lane group 0) is past lk has zero weight in
-  // every lane: its matrix ops are skipped (a uniform branch; for DAM's 50
-  // keys, 2 of the 16 steps).
-  auto step_live = [&](int i) { return (i >> 2) < NKT - 1 || 16 * (i >> 2) + (i & 3) < lk; };
-  const __amdgpu_buffer_rsrc_t ro =
-      make_rsrc(o + (b * lq + q0) * static_cast<int64_t>(dv), nq * dv * 4);
-  const int orow = 4 * g * dv * 4;
-  const int nfull = dv >> 6;
-  // Each 64-column block in four quarters of NKT contraction steps: the next
-  // quarter's V rows (the next block's first, after the last) are read while
-  // this quarter's matrix ops run; the key mask is applied at use.
-  f32x4m vq[2][NKT];
-  if (nfull > 0) {
-#pragma unroll
-    for (int i = 0; i < NKT; ++i)
-      vq[0][i] = *reinterpret_cast<const f32x4m*>(lv_s + vrow(i) + 4 * j);
-  }
-  for (int cb = 0; cb < nfull; ++cb) {
-    const int c = 64 * cb + 4 * j;
-    f32x4m oacc[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) oacc[u] = f32x4m{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int qi = 0; qi < 4; ++qi) {
-      if (qi < 3) {
-#pragma unroll
-        for (int i = 0; i < NKT; ++i)
-          vq[(qi + 1) & 1][i] =
-              *reinterpret_cast<const f32x4m*>(lv_s + vrow((qi + 1) * NKT + i) + c);
-      } else if (cb + 1 < nfull) {
-#pragma unroll
-        for (int i = 0; i < NKT; ++i)
-          vq[0][i] = *reinterpret_cast<const f32x4m*>(lv_s + vrow(i) + c + 64);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < NKT; ++i) {
-        const int st = qi * NKT + i;
-        if (step_live(st)) {
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            oacc[u] = mfma16x16x4(e[st], v_ok(st) ? vq[qi & 1][i][u] : 0.0f, oacc[u]);
-        }
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const f32x4m ov = {oacc[0][r], oacc[1][r], oacc[2][r], oacc[3][r]};
-      __builtin_amdgcn_raw_buffer_store_b128(
-          __builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, ov), ro,
-          orow + (r * dv + c) * 4, 0, 0);
-    }
-  }
-  // The remaining columns, one 16-column tile at a time: lane j takes column
-  // c0 + j; a column past dv reads a masked operand.
-  for (int c0 = 64 * nfull; c0 < dv; c0 += 16) {
-    const int c = c0 + j;
-    const bool c_ok = c < dv;
-    f32x4m oa = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int i = 0; i < 4 * NKT; ++i) {
-      if (step_live(i)) {
-        const float x = lv_s[vrow(i) + (c_ok ? c : 0)];
-        oa = mfma16x16x4(e[i], (v_ok(i) & c_ok) ? x : 0.0f, oa);
-      }
-    }
-    // Plain stores here: a 32-bit buffer store of an accumulator element
-    // was compiled to store element 0 for every r by this toolchain.
-    float* orow_p = o + (b * lq + q0 + 4 * g) * static_cast<int64_t>(dv) + c;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      if ((q0 + 4 * g + r < lq) & c_ok)
-        __builtin_nontemporal_store(oa[r], orow_p + static_cast<int64_t>(r) * dv);
-    }
-  }
-}
-
 // Scores, clipped softmax and O = P V for one wavefront's nq <= 16 queries
 // q0 .. of batch element b, with K_b at lk_s and V_b at lv_s in LDS and the
-// query rows in qf.  With DC != 0 (d = dv = DC), a zero row of dv + 16
-// floats follows V_b, and padding keys read their values from it
-// (attn_pv_stream).  With MID_SYNC the wavefront takes one workgroup barrier
+// query rows in qf.  A zero row of dv + 16 floats follows V_b, and padding
+// keys read their values from it (attn_pv_stream).  With MID_SYNC the wavefront takes one workgroup barrier
 // between the softmax and the value product (V_b still in flight when the
 // scores start).
 template <int NKT, bool WIDE, int DC, bool MID_SYNC = false>
@@ -576,14 +271,14 @@ __device__ __forceinline__ void attn_compute(const float* lk_s, const float* lv_
                                              float scale, Clip clip, int j, int g) {
   constexpr int QB = kAttnQB;
   const int nblk = (d + 15) >> 4;
-  // With DC != 0 (the DAM tile; the host guarantees at most 2 keys in the
-  // last key tile, lk <= 16 (NKT - 1) + 2) those keys' scores are dot
-  // products on the VALU: lane (j, g) sums its own terms t = 16 blk + 4 g + s
+  // The host guarantees at most 2 keys in the last key tile
+  // (lk <= 16 (NKT - 1) + 2): those keys' scores are dot products on the
+  // VALU: lane (j, g) sums its own terms t = 16 blk + 4 g + s
   // of query j, interleaved with the other tiles' matrix ops, and the 4 lanes
   // of query j add their sums.  Only NMT tiles go through the matrix cores:
   // a 16-key tile for 2 keys cost as much as a full one (92.8 -> 82.6 us on
   // the DAM shape).
-  constexpr bool VT = DC != 0 && NKT > 1;
+  constexpr bool VT = NKT > 1;
   constexpr int NMT = VT ? NKT - 1 : NKT;  // key tiles on the matrix cores
   constexpr int NR = VT ? NKT + 1 : NKT;   // K operand rows per lane
 
@@ -619,7 +314,7 @@ __device__ __forceinline__ void attn_compute(const float* lk_s, const float* lv_
           kn[kt] = *reinterpret_cast<const f32x4m*>(lk_s + krow[kt] + 16 * (blk + 1));
       }
       __builtin_amdgcn_sched_barrier(0);
-      const bool t_ok = (DC != 0 && 16 * blk + 16 <= d) || 16 * blk + 4 * g < d;
+      const bool t_ok = (16 * blk + 16 <= d) || 16 * blk + 4 * g < d;
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
 #pragma unroll
@@ -664,58 +359,8 @@ __device__ __forceinline__ void attn_compute(const float* lk_s, const float* lv_
   m = fmaxf(m, row16_partner(m));
   m = fmaxf(m, half32_partner(m));
   const RowShift rs = row_shift(m, clip);
-  if constexpr (DC != 0) {
-    if constexpr (MID_SYNC) __syncthreads();
-    attn_pv_stream<NKT, WIDE, DC, VT>(e, rs, lv_s, o, b, q0, nq, lq, lk, j, g);
-  } else {
-    static_assert(!MID_SYNC, "the mid-item barrier is for the compile-time tile");
-    attn_pv_rows<NKT, WIDE>(e, rs, lv_s, o, b, q0, nq, lq, lk, dv, j, g);
-  }
-}
-
-// Two workgroups of 4 wavefronts per CU, each with its own 80 KiB of LDS:
-// copy K_b and V_b, load Q, wait, compute, one item after another.  With
-// DC != 0 the zero row after V_b is cleared once; no copy writes there.
-template <int NKT, bool WIDE, int DC = 0>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_attention_lds(
-    const float* q, const float* k, const float* v, float* o, int64_t batch, int lq, int lk,
-    int d_in, int dv_in, float scale, Clip clip) {
-  const int d = DC ? DC : d_in;
-  const int dv = DC ? DC : dv_in;
-  __shared__ __attribute__((aligned(16))) float lds[kAttnLdsBytes / 4];
-  float* lk_s = lds;           // K_b: lk x d
-  float* lv_s = lds + lk * d;  // V_b: lk x dv (16-byte aligned: d % 4 == 0)
-  const int lane = __lane_id();
-  const int j = lane & 15;
-  const int g = lane >> 4;
-  const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
-  const int qblocks = (lq + 63) >> 6;
-  const int64_t items = batch * qblocks;
-  if constexpr (DC != 0) {
-    for (int i = threadIdx.x; i < dv + 16; i += 256) lv_s[lk * dv + i] = 0.0f;
-  }
-  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
-    const int64_t b = item / qblocks;
-    const int q0 = static_cast<int>(item - b * qblocks) * 64 + 16 * w;
-    const bool active = q0 < lq;  // wave-uniform
-    const int nq = active ? (lq - q0 < 16 ? lq - q0 : 16) : 0;
-    // The other workgroup on this CU is usually running its matrix ops on
-    // the same SIMDs; a higher wave priority gets these copies and loads
-    // issued first, so the memory work starts early (97.7 -> 95.6 us on the
-    // DAM shape; raising the priority of the matrix-op loops instead made
-    // it 104.4).
-    __builtin_amdgcn_s_setprio(2);
-    attn_copy_kv(lk_s, lv_s, k + b * lk * static_cast<int64_t>(d),
-                 v + b * lk * static_cast<int64_t>(dv), lk * d * 4, lk * dv * 4, w, lane);
-    f32x4m qf[kAttnQB];
-    if (active) attn_load_q<DC>(qf, q, b, q0, nq, lq, d, j, g);
-    __builtin_amdgcn_s_setprio(0);
-    __builtin_amdgcn_s_waitcnt(0);  // this wave's copies and loads
-    __syncthreads();                // everyone's copies
-    if (active)
-      attn_compute<NKT, WIDE, DC>(lk_s, lv_s, qf, o, b, q0, nq, lq, lk, d, dv, scale, clip, j, g);
-    __syncthreads();  // LDS is free for the next item
-  }
+  if constexpr (MID_SYNC) __syncthreads();
+  attn_pv_stream<NKT, WIDE, DC, VT>(e, rs, lv_s, o, b, q0, nq, lq, lk, j, g);
 }
 
 // One workgroup of 8 wavefronts per CU in two teams of 4, with two 80 KiB
@@ -727,12 +372,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // each team per SIMD.  Every wavefront passes the same barriers: one after
 // the first copy, one per phase.  The team that copies has raised priority
 // while it issues, as in k_attention_lds.
-template <int NKT, bool WIDE, int DC = 0>
+template <int NKT, bool WIDE, int DC>
 __global__ __launch_bounds__(512) void k_attention_pp(
     const float* q, const float* k, const float* v, float* o, int64_t batch, int lq, int lk,
-    int d_in, int dv_in, float scale, Clip clip) {
-  const int d = DC ? DC : d_in;
-  const int dv = DC ? DC : dv_in;
+    int, int, float scale, Clip clip) {
+  constexpr int d = DC;
+  constexpr int dv = DC;
   constexpr int kBuf = kAttnLdsBytes / 4;  // floats per buffer
   __shared__ __attribute__((aligned(16))) float lds[2 * kBuf];
   const int lane = __lane_id();
@@ -745,11 +390,9 @@ __global__ __launch_bounds__(512) void k_attention_pp(
   const int64_t items = batch * qblocks;
   // Items of this workgroup: blockIdx.x + n gridDim.x (at least one).
   const int64_t n_items = (items - 1 - blockIdx.x) / gridDim.x + 1;
-  if constexpr (DC != 0) {
-    for (int i = threadIdx.x; i < dv + 16; i += 512) {
-      lds[lk * (d + dv) + i] = 0.0f;
-      lds[kBuf + lk * (d + dv) + i] = 0.0f;
-    }
+  for (int i = threadIdx.x; i < dv + 16; i += 512) {
+    lds[lk * (d + dv) + i] = 0.0f;
+    lds[kBuf + lk * (d + dv) + i] = 0.0f;
   }
   f32x4m qf[kAttnQB];
   auto where = [&](int64_t n, int64_t& b, int& q0, int& nq) {
