@@ -62,9 +62,10 @@ extern "C" {
 
 /* Kernel families reported by softmax_plan(). */
 #define SOFTMAX_KERNEL_NONE 0      /* rows*cols == 0: nothing is launched */
-#define SOFTMAX_KERNEL_PACKED 1    /* cols <= 256 not taken by GROUP_ROWS
-                                      (log and NLL outputs: cols <= 64):
-                                      several rows per wavefront */
+#define SOFTMAX_KERNEL_PACKED 1    /* cols <= 256 not taken by GROUP_ROWS:
+                                      several rows per wavefront (with few
+                                      rows of 65 to 256 columns that are not
+                                      whole strips: WAVE_ROW) */
 #define SOFTMAX_KERNEL_WAVE_ROW 2  /* cols <= 4096: one wavefront per row
                                       (rows that are not whole 16-byte
                                       strips: 128-bit access in the aligned
@@ -82,8 +83,7 @@ extern "C" {
                                       rows that are not whole strips) */
 #define SOFTMAX_KERNEL_GROUP_ROWS 5 /* cols <= 256 in whole 16-byte strips
                                        (cols % 4 == 0, 16-byte aligned x and
-                                       y), probability outputs: G lanes per
-                                       row (G the power of two >= cols / 4),
+                                       y): G lanes per row (G the power of two >= cols / 4),
                                        several rows per wavefront.  Past
                                        about one round of the device's
                                        resident workgroups, rows that fill
@@ -344,8 +344,8 @@ typedef struct softmax_plan_t {
 
 /* The shape fields (kernel, vec_width, lanes_per_row, elems_per_lane,
  * block_threads, chunks_per_row) depend only on the arguments, except that
- * rows of at most 256 columns choose between GROUP_ROWS and PACKED, long
- * rows their chunk size, and rows of 16385 to 24575 columns between
+ * rows of at most 256 columns choose between GROUP_ROWS, PACKED and
+ * WAVE_ROW, long rows their chunk size, and rows of 16385 to 24575 columns between
  * BLOCK_ROW and SPLIT_ROW, by the device's resident workgroups or compute
  * units too;
  * grid, launches and store_delay_ns are those for the current device, and

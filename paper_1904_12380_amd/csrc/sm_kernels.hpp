@@ -13,10 +13,10 @@
 // y as scratch: x is read from HBM once (twice for rows over 2^21 columns)
 // and y is written once.
 //
-//   k_group_rows  cols <= 256 in whole 16-byte strips, probability
-//                 outputs: G lanes per row, each holding one 128-bit strip
-//                 as the coalesced load leaves it; segmented DPP reductions.
-//   k_packed      cols <= 64 otherwise: a persistent workgroup stages tiles
+//   k_group_rows  cols <= 256 in whole 16-byte strips: G lanes per row, each
+//                 holding one 128-bit strip as the coalesced load leaves it;
+//                 segmented DPP reductions.
+//   k_packed      other rows of cols <= 256 (losses: 64): a persistent workgroup stages tiles
 //                 of whole rows in LDS with 128-bit loads, groups of G lanes
 //                 reduce one row each with DPP, and the tile goes back out
 //                 with 128-bit stores; the next tile's loads are issued early.
@@ -452,6 +452,20 @@ __device__ __forceinline__ void store_row(const float (&v)[4 * V], RowShift rs, 
   }
 }
 
+// store_row for a row accessed with its phase (load_strip_ph).
+template <int V, int MODE>
+__device__ __forceinline__ void store_row_ph(const float (&v)[4 * V], RowShift rs, float s,
+                                             float* p, int a, int lane_off, int stride, int lim) {
+  if constexpr (MODE == kLogOut) {
+    const float ls = log_of_sum(s);
+    store_strip_ph<V>(v, [&](float xv) { return log_out(xv, rs, ls); }, p, a, lane_off, stride,
+                      lim);
+  } else {
+    const float rcp = 1.0f / s;
+    store_strip_ph<V>(v, [&](float ev) { return ev * rcp; }, p, a, lane_off, stride, lim);
+  }
+}
+
 // Stores the probabilities of a segment left by segment_online: with the
 // row's shift rs (max M) and rcp = 1/S,
 //     y = max(e * exp(max(mk - M, lo)) * rcp, e_lo * rcp)
@@ -627,7 +641,7 @@ __global__ __launch_bounds__(256) void k_packed(const float* x, float* y,
 }
 
 // (a, aligned) Rows of at most 256 columns made of whole 16-byte strips
-// (cols a multiple of 4, x and y 16-byte aligned), probability outputs.
+// (cols a multiple of 4, x and y 16-byte aligned).
 // G lanes per row (G the power of two >= cols / 4), each lane one 128-bit
 // strip of 4 columns, so a wavefront's load instruction covers 64 / G
 // consecutive rows exactly as the coalesced load leaves them: no LDS and no
@@ -687,10 +701,16 @@ __global__ __launch_bounds__(256) void k_group_rows(const float* x, float* y, in
       const int64_t row = r0 + u * R + rho;
       const float m = seg_max<G>(fmaxf(fmaxf(q[u].x, q[u].y), fmaxf(q[u].z, q[u].w)));
       const RowShift rs = row_shift(m, clip);
-      float e[4] = {exp_shift_clip<MODE>(q[u].x, rs), exp_shift_clip<MODE>(q[u].y, rs),
-                    exp_shift_clip<MODE>(q[u].z, rs), exp_shift_clip<MODE>(q[u].w, rs)};
-      const float rcp = 1.0f / seg_sum<G>(tree_sum(e));
-      const f32x4 out = {e[0] * rcp, e[1] * rcp, e[2] * rcp, e[3] * rcp};
+      float e[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
+      f32x4 out;
+      if constexpr (MODE == kLogOut) {
+        const float ls = log_of_sum(seg_sum<G>(exp_strip<MODE>(e, rs)));
+        out = f32x4{log_out(e[0], rs, ls), log_out(e[1], rs, ls), log_out(e[2], rs, ls),
+                    log_out(e[3], rs, ls)};
+      } else {
+        const float rcp = 1.0f / seg_sum<G>(exp_strip<MODE>(e, rs));
+        out = f32x4{e[0] * rcp, e[1] * rcp, e[2] * rcp, e[3] * rcp};
+      }
       if (col_ok && row < rows) st_stream(y + row * cols + 4 * j, out);
     }
 #pragma unroll
@@ -717,14 +737,14 @@ constexpr int kRowWaves = (V <= 8 && VEC4 && !keeps_logits<MODE>()) ? 4 : 2;
 // over before its writes begin (HBM then serves them in two phases rather
 // than interleaved).
 //
-// PH (probability outputs, 128-bit access): rows of a length that is not a
+// PH (128-bit access): rows of a length that is not a
 // multiple of 4 in 16-byte aligned x and y, each row accessed in the aligned
 // strips around it (load_strip_ph); the row's phase is (row * cols) mod 4.
 template <int V, bool VEC4, int MODE, bool PH = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
     kRowWaves<V, VEC4, MODE>))) void k_wave_row(
     const float* x, float* y, int64_t rows, int64_t cols, Clip clip, uint32_t delay) {
-  static_assert(!PH || (VEC4 && !keeps_logits<MODE>()), "phase access: probability outputs");
+  static_assert(!PH || VEC4, "phase access is 128-bit access");
   const uint64_t t0 = wall_clock();
   const int lane = __lane_id();
   const int wave = threadIdx.x >> 6;
@@ -739,9 +759,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
       const RowShift rs = row_shift(seg_max<64>(array_max(v)), clip);
       const float s = seg_sum<64>(exp_strip<MODE>(v, rs));
       if (delay != 0) wait_until_after(t0 + delay, s);
-      const float rcp = 1.0f / s;
-      store_strip_ph<V>(v, [&](float ev) { return ev * rcp; }, y + row * cols, a, opaque(lane),
-                        64, lim);
+      store_row_ph<V, MODE>(v, rs, s, y + row * cols, a, opaque(lane), 64, lim);
       continue;
     }
     load_strip<V, VEC4>(v, xr, opaque(lane), 64, lim);
@@ -758,7 +776,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
 template <int NT, int V, bool VEC4, int MODE, bool PH = false>
 __global__ __launch_bounds__(NT) void k_block_row(const float* x, float* y, int64_t rows,
                                                   int64_t cols, Clip clip, uint32_t delay) {
-  static_assert(!PH || (VEC4 && !keeps_logits<MODE>()), "phase access: probability outputs");
+  static_assert(!PH || VEC4, "phase access is 128-bit access");
   const uint64_t t0 = wall_clock();
   constexpr int NW = NT / 64;
   __shared__ float red_max[NW];
@@ -774,9 +792,7 @@ __global__ __launch_bounds__(NT) void k_block_row(const float* x, float* y, int6
       const RowShift rs = row_shift(block_max<NW>(array_max(v), red_max), clip);
       const float s = block_sum<NW>(exp_strip<MODE>(v, rs), red_sum);
       if (delay != 0) wait_until_after(t0 + delay, s);
-      const float rcp = 1.0f / s;
-      store_strip_ph<V>(v, [&](float ev) { return ev * rcp; }, y + row * cols, a, opaque(tid),
-                        NT, lim);
+      store_row_ph<V, MODE>(v, rs, s, y + row * cols, a, opaque(tid), NT, lim);
     } else {
       // (The online reduction of the split kernel measured slower here:
       // 23.2 us against 22.5 us on 512 rows of 32768.)
@@ -1039,7 +1055,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
   const float* xr = x + lrow * cols + c0;
 
   constexpr bool ONLINE = !keeps_logits<MODE>() && online_exp<4 * V>();
-  static_assert(!PH || ONLINE, "phase access: the online reduction");
   float v[4 * V];
   float mk[ONLINE ? 4 * V / kOnlineSub : 1];
   float2 part;

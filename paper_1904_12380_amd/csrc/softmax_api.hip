@@ -96,6 +96,28 @@ constexpr int64_t kGroupRowsPackedRoundsDen = 2;
 constexpr int64_t kGroupRowsOneStepNum = 13;  // kGroupRowsOneStep = 1.3 rounds
 constexpr int64_t kGroupRowsOneStepDen = 10;
 
+// Rows of 65 to 256 columns that are not whole 16-byte strips: with few rows
+// one wavefront per row and 32-bit access instead of packed tiles, whose
+// tiles then go through registers, LDS and two barriers one after another.
+// Measured on 12 widths at 300 to 8000 rows: up to 4 rows per CU the
+// wavefronts were 1-26% faster on 65 to 190 columns (300 x 102 2.4 against
+// 3.2 us; 3000 x 130 3.4 against 3.2), and on 193 to 255 columns up to 32 per
+// CU (300 x 250 2.7 against 3.7, 4000 x 210 3.8 against 4.1, 8000 x 193
+// level).
+constexpr int64_t kPackedWideCols = 192;
+constexpr int64_t kPackedMinRowsPerCU = 4;
+constexpr int64_t kPackedMinRowsPerCUWide = 32;
+// Log rows past this fill a wavefront's four 32-bit loads: 67108 x 250 ran
+// 25.1 us so and 26.1 packed (65793 x 255 26.8 and 26.3, 129055 x 130 35.2
+// and 24.6).
+constexpr int64_t kLogPackedMaxCols = 224;
+// Log rows that are not whole strips: the row phase pays once the rows fill
+// the device (8188 x 2049 28.5 us against 48.2 with 32-bit access, 2795 x 6001
+// 25.3 against 30.6, 1023 x 2049 7.5 against 8.3; 512 x 4093 7.2 against 5.8,
+// 192 x 4093 6.8 against 4.3), and not in the split kernel, which keeps the
+// logits (559 x 30003 31.4 against 30.4 us, 41 x 50001 9.7 against 9.0).
+constexpr int64_t kLogPhaseMinRowsPerCU = 3;
+
 // Split rows, one pass: a row spans at most this many workgroups (the
 // exchange is read by one wavefront, one slot per lane).  Chunk shapes,
 // threads x 4-element strips per lane: probability and log rows take 256 x 8
@@ -132,6 +154,7 @@ constexpr int64_t kSmallChunkMaxChunks = 8;
 constexpr int64_t kSplitSparseNum = 5;  // workgroups per CU, 5/8
 constexpr int64_t kSplitSparseDen = 8;
 constexpr int64_t kSplitSparseMaxChunks = 40;
+constexpr int64_t kLogSplitSparseDen = 4;
 constexpr int64_t kSplitThinPerCU = 2;
 constexpr int64_t kSplitThinMaxChunks = 32;
 constexpr int64_t kSplitThinPadDen = 32;  // extra padding of at least cols / 32
@@ -328,7 +351,7 @@ const void* packed_shape_fn(const Shape& s) {
   if (s.g == 1) return packed_fn<1, VEC4, EM>(s.epl, std::make_integer_sequence<int, 16>{});
   if (s.g == 2) return packed_fn<2, VEC4, EM>(s.epl, std::make_integer_sequence<int, 8>{});
   if (s.g == 4) return packed_fn<4, VEC4, EM>(s.epl, std::make_integer_sequence<int, 8>{});
-  if constexpr (EM == kExpAccurate || EM == kExpWide || EM == kExpFast) {
+  if constexpr (EM != kNllOut) {
     if (s.g == 8) return packed_fn<8, VEC4, EM>(s.epl, std::make_integer_sequence<int, 8>{});
     if (s.g == 16) return packed_fn<16, VEC4, EM>(s.epl, std::make_integer_sequence<int, 8>{});
   }
@@ -345,7 +368,7 @@ const void* shape_fn(const Shape& s, bool stats_pass) {
   auto cast = [](auto f) { return reinterpret_cast<const void*>(f); };
   switch (s.kernel) {
     case SOFTMAX_KERNEL_GROUP_ROWS:
-      if constexpr (VEC4 && (EM == kExpAccurate || EM == kExpWide || EM == kExpFast)) {
+      if constexpr (VEC4) {
         if (s.v == 1) return group_rows_fn<1, EM>(s.g);
         if (s.v == 2) return group_rows_fn<2, EM>(s.g);
       }
@@ -354,7 +377,7 @@ const void* shape_fn(const Shape& s, bool stats_pass) {
       return packed_shape_fn<EM, VEC4>(s);
     case SOFTMAX_KERNEL_WAVE_ROW:
       if (s.ph) {
-        if constexpr (VEC4 && (EM == kExpAccurate || EM == kExpWide || EM == kExpFast)) {
+        if constexpr (VEC4) {
           switch (s.v) {
             case 1: return cast(&k_wave_row<1, true, EM, true>);
             case 2: return cast(&k_wave_row<2, true, EM, true>);
@@ -378,7 +401,7 @@ const void* shape_fn(const Shape& s, bool stats_pass) {
       }
     case SOFTMAX_KERNEL_BLOCK_ROW:
       if (s.ph) {
-        if constexpr (VEC4 && (EM == kExpAccurate || EM == kExpWide || EM == kExpFast)) {
+        if constexpr (VEC4) {
           switch (s.v) {
             case 2: return cast(&k_block_row<kBlockThreads, 2, true, EM, true>);
             case 4: return cast(&k_block_row<kBlockThreads, 4, true, EM, true>);
@@ -400,7 +423,7 @@ const void* shape_fn(const Shape& s, bool stats_pass) {
                           : cast(&k_split_apply<kSplitThreads, kSplitV, VEC4, EM>);
       }
       if (s.ph) {
-        if constexpr (VEC4 && (EM == kExpAccurate || EM == kExpWide || EM == kExpFast)) {
+        if constexpr (VEC4 && EM != kLogOut) {
           if (s.threads == 256 && s.v == 8) return cast(&k_split_onepass<256, 8, true, EM, true>);
           if (s.threads == 512 && s.v == 8) return cast(&k_split_onepass<512, 8, true, EM, true>);
         }
@@ -512,29 +535,29 @@ void phase_row_shape(int64_t cols, Shape* s) {
 // library_shape refines it for short rows by the row count and the device.
 Shape default_shape(const float* x, const float* y, int64_t cols, int em) {
   Shape s;
-  const bool prob = em != kLogOut && em != kNllOut;
+  const bool loss = em == kNllOut;  // rows of at most kPackedMaxCols columns
   s.vec4 = can_vec4(cols <= kPackedMaxCols ? SOFTMAX_KERNEL_PACKED : SOFTMAX_KERNEL_SPLIT_ROW,
                     x, y, cols);
-  if (prob && cols <= kGroupRowsMaxCols && can_vec4(SOFTMAX_KERNEL_GROUP_ROWS, x, y, cols)) {
+  if (!loss && cols <= kGroupRowsMaxCols && can_vec4(SOFTMAX_KERNEL_GROUP_ROWS, x, y, cols)) {
     s.kernel = SOFTMAX_KERNEL_GROUP_ROWS;
     s.vec4 = true;
     s.threads = 256;
     s.g = group_rows_lanes(cols);
     s.v = 2;
-  } else if (cols <= (prob ? kPackedProbMaxCols : kPackedMaxCols)) {
+  } else if (cols <= kPackedProbMaxCols) {
     // G lanes per row with at most 16 columns per lane.
     s.kernel = SOFTMAX_KERNEL_PACKED;
     s.vec4 = can_vec4(SOFTMAX_KERNEL_PACKED, x, y, cols);
     s.threads = 256;
     s.g = packed_lanes(cols);
     s.epl = static_cast<int>(ceil_div(cols, s.g));
-  } else if (prob && phase_rows(x, y, cols)) {
+  } else if (phase_rows(x, y, cols)) {
     // Rows that are not whole 16-byte strips, in aligned x and y: 128-bit
     // access in the aligned strips around each row.
     s.vec4 = true;
     s.ph = true;
     phase_row_shape(cols, &s);
-  } else if (prob && split_phase_rows(x, y, cols)) {
+  } else if (split_phase_rows(x, y, cols)) {
     // Long rows that are not whole 16-byte strips, in aligned x and y: the
     // one-pass split kernel with the row phase.
     s.kernel = SOFTMAX_KERNEL_SPLIT_ROW;
@@ -584,8 +607,7 @@ bool requested_shape(const softmax_plan_t& want, const float* x, const float* y,
   const bool row_kernel =
       s.kernel == SOFTMAX_KERNEL_WAVE_ROW || s.kernel == SOFTMAX_KERNEL_BLOCK_ROW;
   // The same for split rows (one pass, 8192- or 16384-column chunks).
-  if (s.vec4 && s.kernel == SOFTMAX_KERNEL_SPLIT_ROW && split_phase_rows(x, y, cols) &&
-      em != kLogOut) {
+  if (s.vec4 && s.kernel == SOFTMAX_KERNEL_SPLIT_ROW && split_phase_rows(x, y, cols)) {
     s.ph = true;
     s.threads = want.block_threads;
     s.v = want.elems_per_lane / 4;
@@ -595,7 +617,7 @@ bool requested_shape(const softmax_plan_t& want, const float* x, const float* y,
     *out = s;
     return true;
   }
-  if (s.vec4 && row_kernel && phase_rows(x, y, cols) && em != kLogOut) {
+  if (s.vec4 && row_kernel && phase_rows(x, y, cols)) {
     const int64_t span = cols + 3;
     if (span > (s.kernel == SOFTMAX_KERNEL_WAVE_ROW ? kWaveRowMaxCols : kSplitMinColsProb))
       return false;
@@ -617,7 +639,7 @@ bool requested_shape(const softmax_plan_t& want, const float* x, const float* y,
       s.v = 2;
       break;
     case SOFTMAX_KERNEL_PACKED:
-      if (cols > (em == kLogOut ? kPackedMaxCols : kPackedProbMaxCols))
+      if (cols > kPackedProbMaxCols)
         return false;
       s.threads = 256;
       s.g = packed_lanes(cols);
@@ -705,6 +727,27 @@ int group_rows_steps(int64_t rows, int em, int dev, const DeviceFacts& f, Shape*
   return SOFTMAX_OK;
 }
 
+// The shape of rows of more than kPackedMaxCols columns read with 32-bit
+// access.
+Shape scalar_row_shape(int64_t cols) {
+  Shape s;
+  if (cols <= kWaveRowMaxColsScalar) {
+    s.kernel = SOFTMAX_KERNEL_WAVE_ROW;
+    s.threads = 256;
+    s.v = static_cast<int>(pow2_at_least(ceil_div(cols, 256)));
+  } else if (cols <= kSplitMinColsProb) {
+    s.kernel = SOFTMAX_KERNEL_BLOCK_ROW;
+    s.threads = kBlockThreads;
+    s.v = static_cast<int>(std::max<int64_t>(2, pow2_at_least(ceil_div(cols, 4096))));
+  } else {
+    s.kernel = SOFTMAX_KERNEL_SPLIT_ROW;
+    s.threads = ceil_div(cols, int64_t(4) * 8 * 256) <= kSmallChunkMaxChunks ? 256 : 512;
+    s.v = 8;
+    s.two_pass = row_chunks(s, cols) > kOnePassMaxChunks;
+  }
+  return s;
+}
+
 // The library's shape once rows and the device are known: rows of at most
 // 256 columns in whole strips take the grouped-rows kernel or the packed
 // kernel by the rules measured above (kGroupRowsMinFill, kGroupRowsOneStep
@@ -713,7 +756,15 @@ int group_rows_steps(int64_t rows, int em, int dev, const DeviceFacts& f, Shape*
 int library_shape(const float* x, const float* y, int64_t rows, int64_t cols, int em, int dev,
                   const DeviceFacts& f, Shape* out) {
   Shape s = default_shape(x, y, cols, em);
-  if (s.kernel == SOFTMAX_KERNEL_GROUP_ROWS) {
+  if ((s.kernel == SOFTMAX_KERNEL_PACKED && s.g >= 8 &&
+       (rows <= f.cus * (cols > kPackedWideCols ? kPackedMinRowsPerCUWide : kPackedMinRowsPerCU) ||
+        (em == kLogOut && cols > kLogPackedMaxCols))) ||
+      (em == kLogOut && s.ph &&
+       (s.kernel == SOFTMAX_KERNEL_SPLIT_ROW || rows < kLogPhaseMinRowsPerCU * f.cus))) {
+    // 32-bit access, the row in a wavefront's (longer rows: a workgroup's)
+    // registers.
+    s = scalar_row_shape(cols);
+  } else if (s.kernel == SOFTMAX_KERNEL_GROUP_ROWS) {
     Shape steps = s;
     int rc = group_rows_steps(rows, em, dev, f, &steps);  // steps.v == 1: a small launch
     int64_t resident = 0;                                // at U = 2
@@ -733,7 +784,7 @@ int library_shape(const float* x, const float* y, int64_t rows, int64_t cols, in
       s.epl = static_cast<int>(ceil_div(cols, s.g));
     }
   } else if (s.kernel == SOFTMAX_KERNEL_SPLIT_ROW && !s.two_pass && s.threads == 512 &&
-             s.v == 8 && em != kLogOut) {
+             s.v == 8) {
     // Probability rows in 16384-column chunks: 8192-column chunks instead
     // by launches and grid fill (kSplitSparseNum, kSplitThinPerCU).
     Shape small = s;
@@ -758,7 +809,12 @@ int library_shape(const float* x, const float* y, int64_t rows, int64_t cols, in
                           pad_more * kSplitThinPadDen >= cols;
         const bool padded = grid512 < kSplitWidePerCU * f.cus && c256 <= kSplitThinMaxChunks &&
                             pad_more * kSplitWidePadDen >= cols;
-        if (fewer_launches || sparse || thin || padded) s = small;
+        // Log rows keep their logits next to the exponentials and gain less
+        // from the small chunks: only at under a quarter of a workgroup per
+        // CU (7 x 100000 7.5 -> 7.2 us; 20 x 100000 8.2 -> 8.4).
+        const bool few = em == kLogOut ? grid512 * kLogSplitSparseDen < f.cus
+                                       : sparse || thin || padded;
+        if (fewer_launches || few) s = small;
       }
     }
   } else if (s.kernel == SOFTMAX_KERNEL_SPLIT_ROW && !s.two_pass && !s.ph && s.vec4 &&
