@@ -189,20 +189,37 @@ def softmax_fwd_ptr(x_ptr: int, y_ptr: int, rows: int, cols: int,
     return int(load_library().softmax_fwd(x_ptr, y_ptr, rows, cols, stream_handle))
 
 
+_torch_mod = None
+_raw_stream = None  # device index -> handle of its current stream
+_get_device = None  # () -> index of the current device
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_mod, _raw_stream, _get_device
+    if _torch_mod is None:
+        import torch
+        # The lookups behind torch.cuda.current_stream() and current_device()
+        # without the Stream object that the former builds on every call
+        # (2.7 us of a 10 us call on the host).
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda index: torch.cuda.current_stream(index).cuda_stream)
+        _get_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+        _torch_mod = torch
+    return _torch_mod
 
 
-def _stream_handle(stream) -> int:
-    torch = _torch()
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return int(stream.cuda_stream)
+def _run(fn, device, stream, args):
+    """The C call ``fn(*args, stream handle)`` with ``device`` current, on
+    ``stream`` or else the device's current torch stream."""
+    index = device.index
+    if _get_device() == index:
+        return fn(*args, _raw_stream(index) if stream is None else int(stream.cuda_stream))
+    with _torch_mod.cuda.device(index):
+        return fn(*args, _raw_stream(index) if stream is None else int(stream.cuda_stream))
 
 
 def _check_f32_cuda(t, name: str):
-    torch = _torch()
+    torch = _torch_mod or _torch()
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.dtype != torch.float32:
@@ -221,12 +238,11 @@ def softmax_fwd_clip_ptr(x_ptr: int, y_ptr: int, rows: int, cols: int, clip_lo: 
 
 
 def _out_for(x, out):
-    torch = _torch()
     _check_f32_cuda(x, "x")
     if x.dim() != 2:
         raise ValueError("x must be 2-D [rows, cols]")
     if out is None:
-        return torch.empty_like(x)
+        return _torch_mod.empty_like(x)
     _check_f32_cuda(out, "out")
     if out.shape != x.shape or out.device != x.device:
         raise ValueError("out must match x in shape and device")
@@ -239,12 +255,10 @@ def softmax_fwd(x, out=None, stream=None):
 
     ``out`` may be ``x`` itself (in place).  Runs on ``stream`` (default: the
     current torch stream) and returns without synchronising."""
-    torch = _torch()
     out = _out_for(x, out)
     rows, cols = x.shape
-    with torch.cuda.device(x.device):
-        rc = softmax_fwd_ptr(x.data_ptr(), out.data_ptr(), rows, cols,
-                             _stream_handle(stream))
+    rc = _run(load_library().softmax_fwd, x.device, stream,
+              (x.data_ptr(), out.data_ptr(), rows, cols))
     if rc != OK:
         raise SoftmaxError(rc, "softmax_fwd")
     return out
@@ -252,12 +266,10 @@ def softmax_fwd(x, out=None, stream=None):
 
 def softmax_fwd_planned(x, plan: dict, out=None, stream=None):
     """softmax_fwd with a caller-chosen kernel (see softmax_fwd_planned_ptr)."""
-    torch = _torch()
     out = _out_for(x, out)
     rows, cols = x.shape
-    with torch.cuda.device(x.device):
-        rc = softmax_fwd_planned_ptr(x.data_ptr(), out.data_ptr(), rows, cols, plan,
-                                     _stream_handle(stream))
+    rc = _run(lambda *a: softmax_fwd_planned_ptr(*a[:4], plan, a[4]), x.device, stream,
+              (x.data_ptr(), out.data_ptr(), rows, cols))
     if rc != OK:
         raise SoftmaxError(rc, "softmax_fwd_planned")
     return out
@@ -266,12 +278,10 @@ def softmax_fwd_planned(x, plan: dict, out=None, stream=None):
 def softmax_fwd_clip(x, clip_lo: float, out=None, stream=None):
     """softmax_fwd with the clip bound as an argument: any value <= CLIP_MAX,
     or -inf for no clip."""
-    torch = _torch()
     out = _out_for(x, out)
     rows, cols = x.shape
-    with torch.cuda.device(x.device):
-        rc = softmax_fwd_clip_ptr(x.data_ptr(), out.data_ptr(), rows, cols, clip_lo,
-                                  _stream_handle(stream))
+    rc = _run(load_library().softmax_fwd_clip, x.device, stream,
+              (x.data_ptr(), out.data_ptr(), rows, cols, float(clip_lo)))
     if rc != OK:
         raise SoftmaxError(rc, "softmax_fwd_clip")
     return out
@@ -287,12 +297,10 @@ def softmax_fwd_approx_ptr(x_ptr: int, y_ptr: int, rows: int, cols: int, clip_lo
 def softmax_fwd_approx(x, clip_lo: float = CLIP_LO, out=None, stream=None):
     """softmax_fwd_clip with the fast fp32 exponential (looser, stated
     bound: 2e-6 + 1.5e-7 |x - max| relative)."""
-    torch = _torch()
     out = _out_for(x, out)
     rows, cols = x.shape
-    with torch.cuda.device(x.device):
-        rc = softmax_fwd_approx_ptr(x.data_ptr(), out.data_ptr(), rows, cols, clip_lo,
-                                    _stream_handle(stream))
+    rc = _run(load_library().softmax_fwd_approx, x.device, stream,
+              (x.data_ptr(), out.data_ptr(), rows, cols, float(clip_lo)))
     if rc != OK:
         raise SoftmaxError(rc, "softmax_fwd_approx")
     return out
@@ -307,12 +315,10 @@ def softmax_log_fwd_ptr(x_ptr: int, y_ptr: int, rows: int, cols: int, clip_lo: f
 
 def softmax_log_fwd(x, clip_lo: float = CLIP_LO, out=None, stream=None):
     """Row-wise log of the clipped softmax, y = max(x - M, clip_lo) - ln S."""
-    torch = _torch()
     out = _out_for(x, out)
     rows, cols = x.shape
-    with torch.cuda.device(x.device):
-        rc = softmax_log_fwd_ptr(x.data_ptr(), out.data_ptr(), rows, cols, clip_lo,
-                                 _stream_handle(stream))
+    rc = _run(load_library().softmax_log_fwd, x.device, stream,
+              (x.data_ptr(), out.data_ptr(), rows, cols, float(clip_lo)))
     if rc != OK:
         raise SoftmaxError(rc, "softmax_log_fwd")
     return out
@@ -341,12 +347,12 @@ def softmax_nll_fwd(x, labels, clip_lo: float = CLIP_LO, out=None, stream=None):
         raise ValueError("labels must be contiguous [rows] on x's device")
     if out is None:
         out = torch.empty(rows, dtype=torch.float32, device=x.device)
-    _check_f32_cuda(out, "out")
-    if out.shape != (rows,) or out.device != x.device:
-        raise ValueError("out must be [rows] on x's device")
-    with torch.cuda.device(x.device):
-        rc = softmax_nll_fwd_ptr(x.data_ptr(), labels.data_ptr(), out.data_ptr(), rows, cols,
-                                 clip_lo, _stream_handle(stream))
+    else:
+        _check_f32_cuda(out, "out")
+        if out.shape != (rows,) or out.device != x.device:
+            raise ValueError("out must be [rows] on x's device")
+    rc = _run(load_library().softmax_nll_fwd, x.device, stream,
+              (x.data_ptr(), labels.data_ptr(), out.data_ptr(), rows, cols, float(clip_lo)))
     if rc != OK:
         raise SoftmaxError(rc, "softmax_nll_fwd")
     return out
@@ -376,16 +382,16 @@ def softmax_attention_fwd(q, k, v, scale=None, clip_lo: float = CLIP_LO, out=Non
         raise ValueError("q, k, v shapes do not match")
     lk, dv = k.shape[1], v.shape[2]
     if scale is None:
-        scale = float(torch.tensor(1.0 / max(d, 1) ** 0.5, dtype=torch.float32))
+        scale = ctypes.c_float(1.0 / max(d, 1) ** 0.5).value
     if out is None:
         out = torch.empty((b, lq, dv), dtype=torch.float32, device=q.device)
     else:
         _check_f32_cuda(out, "out")
         if tuple(out.shape) != (b, lq, dv):
             raise ValueError("out must be [batch, lq, dv]")
-    with torch.cuda.device(q.device):
-        rc = softmax_attention_fwd_ptr(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
-                                       b, lq, lk, d, dv, scale, clip_lo, _stream_handle(stream))
+    rc = _run(load_library().softmax_attention_fwd, q.device, stream,
+              (q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), b, lq, lk, d, dv,
+               float(scale), float(clip_lo)))
     if rc != OK:
         raise SoftmaxError(rc, "softmax_attention_fwd")
     return out
@@ -409,10 +415,9 @@ def softmax_exp_probe(x, m, out=None, stream=None, clip_lo: float = CLIP_LO,
     if out is None:
         out = torch.empty_like(x)
     _check_f32_cuda(out, "out")
-    with torch.cuda.device(x.device):
-        rc = int(load_library().softmax_exp_probe(
-            x.data_ptr(), None if m is None else m.data_ptr(), out.data_ptr(), x.numel(),
-            float(clip_lo), int(approx), _stream_handle(stream)))
+    rc = _run(load_library().softmax_exp_probe, x.device, stream,
+              (x.data_ptr(), None if m is None else m.data_ptr(), out.data_ptr(), x.numel(),
+               float(clip_lo), int(approx)))
     if rc != OK:
         raise SoftmaxError(rc, "softmax_exp_probe")
     return out
@@ -427,9 +432,8 @@ def softmax_copy_probe(x, out=None, stream=None):
     _check_f32_cuda(out, "out")
     if out.numel() != x.numel():
         raise ValueError("out must have as many elements as x")
-    with torch.cuda.device(x.device):
-        rc = int(load_library().softmax_copy_probe(
-            x.data_ptr(), out.data_ptr(), x.numel(), _stream_handle(stream)))
+    rc = _run(load_library().softmax_copy_probe, x.device, stream,
+              (x.data_ptr(), out.data_ptr(), x.numel()))
     if rc != OK:
         raise SoftmaxError(rc, "softmax_copy_probe")
     return out
