@@ -38,7 +38,7 @@ namespace xch {
 
 constexpr int kEntries = 4096;        // row entries per device
 constexpr int kEntrySlots = 64;       // 64-bit slots per entry: one per workgroup of the row
-constexpr int kHeaderWords = 8;       // owner, departures: one 64-byte line
+constexpr int kHeaderWords = 8;       // owner, departures (two counts): one 64-byte line
 constexpr int kEntryWords = kHeaderWords + kEntrySlots;   // 576 bytes
 constexpr int kDiagWord = kEntries * kEntryWords;          // give-up counters
 constexpr int kDiagWords = 32;
@@ -109,15 +109,24 @@ struct XchArgs {
   uint32_t unused;
 };
 
+// Where the entry of row `lrow` of the launch lies.
+__device__ __forceinline__ uint64_t* find_entry(const XchArgs& a, int lrow) {
+  const int e = static_cast<int>((a.base + static_cast<uint32_t>(lrow)) & (xch::kEntries - 1));
+  return a.scratch + int64_t(e) * xch::kEntryWords;
+}
+
+// The owner word of an entry that holds row `lrow` of the launch.
+__device__ __forceinline__ uint64_t row_tag(const XchArgs& a, int lrow) {
+  const uint64_t tag =
+      xch::mix64(xch::mix64(a.key) ^ (static_cast<uint64_t>(lrow) * 0x9E3779B97F4A7C15ull));
+  return tag == 0 ? 1 : tag;
+}
+
 // Entry of row `lrow` of the launch, joined (or, with a.join == 0, found)
 // by the calling lane; null once `deadline` has passed.
 __device__ __forceinline__ uint64_t* row_entry(const XchArgs& a, int lrow, uint64_t deadline) {
-  using namespace xch;
-  const uint64_t h = mix64(a.key);
-  const int e = static_cast<int>((a.base + static_cast<uint32_t>(lrow)) & (kEntries - 1));
-  uint64_t tag = mix64(h ^ (static_cast<uint64_t>(lrow) * 0x9E3779B97F4A7C15ull));
-  if (tag == 0) tag = 1;
-  uint64_t* entry = a.scratch + int64_t(e) * kEntryWords;
+  const uint64_t tag = row_tag(a, lrow);
+  uint64_t* entry = find_entry(a, lrow);
   while (true) {
     uint64_t seen;
     if (a.join) {
@@ -127,7 +136,7 @@ __device__ __forceinline__ uint64_t* row_entry(const XchArgs& a, int lrow, uint6
       seen = expected;  // 0 if this call claimed it, else the owner it found
       if (seen == 0 || seen == tag) return entry;
     } else {
-      seen = ld_agent(&entry[0]);
+      seen = xch::ld_agent(&entry[0]);
       if (seen == tag) return entry;
     }
     if (static_cast<int64_t>(wall_clock() - deadline) > 0) return nullptr;

@@ -27,9 +27,7 @@
 //   k_split_onepass   rows of up to 64 chunks: one workgroup per chunk,
 //                 partials exchanged between the row's workgroups in the
 //                 middle of the kernel, x read once.
-//   k_split_stats / k_split_apply   longer rows: G workgroups per row; the
-//                 first pass writes a (max, sum) partial per chunk, the
-//                 second merges them and writes the chunk's outputs.
+//   (longer rows: k_long_stats / k_long_apply in sm_long.hpp)
 //
 // In-place calls (x == y) are safe in every kernel: each element is read
 // into registers (or LDS) by the workgroup that later writes it, before any
@@ -885,103 +883,6 @@ __device__ __forceinline__ float2 chunk_partial(float (&v)[4 * V], int lim, Clip
   }
   if (m == kNegInf) s = static_cast<float>(lim);
   return make_float2(m, s);
-}
-
-// (c, split, two passes) for rows longer than a one-pass launch can hold.
-// The launch has WPR <= 64 workgroups per row; workgroup w of a row takes
-// the row's chunks w, w + WPR, ...  Pass 1 (k_split_stats) joins the row's
-// entry and leaves each workgroup's merged partial in its slot; pass 2
-// (k_split_apply) finds the entry, merges the row's WPR slots, writes the
-// chunks' outputs, and the last workgroup of the row releases the entry.
-// x is read twice.
-template <int NT, int V, bool VEC4, int MODE>
-__global__ __launch_bounds__(NT) void k_split_stats(const float* x, XchArgs xa, int64_t cols,
-                                                    int wpr, int64_t chunks, Clip clip) {
-  const uint64_t t0 = wall_clock();
-  constexpr int NW = NT / 64;
-  constexpr int64_t CH = int64_t(4) * V * NT;
-  __shared__ float red_max[NW];
-  __shared__ float red_sum[NW];
-  const int tid = threadIdx.x;
-  const int b = blockIdx.x;
-  const int lrow = b / wpr;
-  const int w = b - lrow * wpr;
-  float m = kNegInf;
-  float s = 0.0f;
-  for (int64_t g = w; g < chunks; g += wpr) {
-    const int64_t c0 = g * CH;
-    const int lim = seg_len(cols, c0, CH);
-    float v[4 * V];
-    load_strip<V, VEC4>(v, x + lrow * cols + c0, tid, NT, lim);
-    const float2 p = chunk_partial<NW, V, MODE>(v, lim, clip, red_max, red_sum);
-    const float mm = fmaxf(m, p.x);
-    if (mm == kNegInf) {
-      s = s + p.y;
-    } else {
-      const RowShift rs = row_shift(mm, clip);
-      const float a = s == 0.0f ? 0.0f : s * exp_shift_clip<exp_mode<MODE>()>(m, rs);
-      s = a + p.y * exp_shift_clip<exp_mode<MODE>()>(p.x, rs);
-    }
-    m = mm;
-    __syncthreads();  // red_max / red_sum are reused by the next chunk
-  }
-  if (tid < 64) {
-    uint64_t* entry = wave_entry(xa, lrow, t0 + xa.limit_ticks);
-    if (tid == 0 && entry != nullptr) xch::st_agent(&entry_slots(entry)[w], encode_pair(m, s));
-  }
-}
-
-template <int NT, int V, bool VEC4, int MODE>
-__global__ __launch_bounds__(NT) void k_split_apply(const float* x, float* y, XchArgs xa,
-                                                    int64_t cols, int wpr, int64_t chunks,
-                                                    Clip clip) {
-  const uint64_t t0 = wall_clock();
-  constexpr int64_t CH = int64_t(4) * V * NT;
-  __shared__ float bcast[2];
-  const int tid = threadIdx.x;
-  const int lane = __lane_id();
-  const int b = blockIdx.x;
-  const int lrow = b / wpr;
-  const int w = b - lrow * wpr;
-  uint64_t* entry = nullptr;  // wavefront 0 only
-  if (tid < 64) {
-    entry = wave_entry(xa, lrow, t0 + xa.limit_ticks);
-    float2 ms = make_float2(__builtin_nanf(""), __builtin_nanf(""));
-    if (entry != nullptr) {
-      const uint64_t q = lane < wpr ? xch::ld_agent(&entry_slots(entry)[lane]) : ~0ull;
-      const float pm = lane < wpr ? decode_m(q) : kNegInf;
-      const float ps = lane < wpr ? decode_s(q) : 0.0f;
-      ms = merge_lanes<exp_mode<MODE>()>(pm, ps, clip);
-    }
-    if (tid == 0) {
-      bcast[0] = ms.x;
-      bcast[1] = ms.y;
-    }
-  }
-  __syncthreads();
-  const RowShift rs = row_shift(bcast[0], clip);
-  const float srow = bcast[1];
-  for (int64_t g = w; g < chunks; g += wpr) {
-    const int64_t c0 = g * CH;
-    const int lim = seg_len(cols, c0, CH);
-    float v[4 * V];
-    load_strip<V, VEC4>(v, x + lrow * cols + c0, tid, NT, lim);
-    if constexpr (!keeps_logits<MODE>()) {
-#pragma unroll
-      for (int i = 0; i < 4 * V; ++i) v[i] = exp_shift_clip<MODE>(v[i], rs);
-    }
-    store_row<V, VEC4, MODE>(v, rs, srow, y + lrow * cols + c0, tid, NT, lim);
-  }
-  if (entry != nullptr && tid < 64) {
-    // The slot reads have returned (the outputs above depend on them).
-    uint32_t last = 0;
-    if (tid == 0) last = depart_entry(entry, wpr, 1u) ? 1u : 0u;
-    last = __builtin_amdgcn_readfirstlane(last);
-    if (last) {
-      if (lane < wpr) xch::st_agent(&entry_slots(entry)[lane], 0ull);
-      if (tid == 0) release_entry(entry);
-    }
-  }
 }
 
 // ---------------------------------------------------------------------------

@@ -73,13 +73,12 @@ __device__ __forceinline__ float nll_loss(float xl, bool bad, float m, float s, 
 
 // The lane's share of the segment p[0, n): thread t of NT.  Whole aligned
 // 16-byte strips, U per lane and step, the next step's loads issued
-// before this step is folded in; the up to six columns outside them go one
-// each to the first threads.
-
-// `after_first` runs once the first step's loads are issued (the label's
-// logit is loaded there: before them, the loads would wait for the label).
-template <int NT, int U, typename F>
-__device__ __forceinline__ NllSum nll_stream(const float* p, int64_t n, int t, F after_first) {
+// before this step is folded in (Sum::add); the up to six columns outside them
+// go one each to the first threads.  `after_first` runs once the first step's
+// loads are issued (the label's logit is loaded there: before them, the loads
+// would wait for the label).  NTL: streaming loads.
+template <int NT, int U, bool NTL, typename Sum, typename F>
+__device__ __forceinline__ Sum stream_sum(const float* p, int64_t n, int t, F after_first) {
   const int64_t to_aligned = (4 - ((reinterpret_cast<uintptr_t>(p) >> 2) & 3)) & 3;
   const int64_t head = to_aligned < n ? to_aligned : n;
   const float* ps = p + head;
@@ -89,21 +88,24 @@ __device__ __forceinline__ NllSum nll_stream(const float* p, int64_t n, int t, F
   float edge = kNegInf;
   if (t < head) edge = p[t];
   if (t >= head && t - head < tail) edge = ps[4 * strips + t - head];
-  NllSum acc;
+  Sum acc;
   acc.m = fmaxf(acc.m, edge);
   acc.s = edge == kNegInf ? 0.0f : 1.0f + (edge - edge);  // NaN for a NaN or +inf edge
   f32x4 q[U];
+  auto ld = [](const float* a) {
+    return NTL ? ld_stream(a) : *reinterpret_cast<const f32x4*>(a);
+  };
   auto load = [&](int64_t i0) {
     const float* pi = ps + 4 * i0;  // uniform base, 32-bit lane offsets
     if (i0 + NT * U <= strips) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) q[u] = ld_stream(pi + 4 * (t + NT * u));
+      for (int u = 0; u < U; ++u) q[u] = ld(pi + 4 * (t + NT * u));
     } else {
       const int left = static_cast<int>(strips - i0);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         q[u] = f32x4{kNegInf, kNegInf, kNegInf, kNegInf};
-        if (t + NT * u < left) q[u] = ld_stream(pi + 4 * (t + NT * u));
+        if (t + NT * u < left) q[u] = ld(pi + 4 * (t + NT * u));
       }
     }
   };
@@ -123,6 +125,11 @@ __device__ __forceinline__ NllSum nll_stream(const float* p, int64_t n, int t, F
     acc.add(v);
   }
   return acc;
+}
+
+template <int NT, int U, typename F>
+__device__ __forceinline__ NllSum nll_stream(const float* p, int64_t n, int t, F after_first) {
+  return stream_sum<NT, U, true, NllSum>(p, n, t, after_first);
 }
 
 // (m, s) over the NT threads' shares; the same bits on every thread.

@@ -12,6 +12,7 @@
 #include "../../include/softmax_mi355x.h"
 #include "sm_host.hpp"
 #include "sm_kernels.hpp"
+#include "sm_long.hpp"
 #include "sm_nll.hpp"
 
 // The exchange table of rows split over several workgroups (layout in
@@ -177,12 +178,21 @@ constexpr int64_t kBlockOverSplitMinRowsDen = 3;   // rows >= CUs / 3
 constexpr int64_t kBlockOverSplitMaxRowsNum = 15;  // rows <= CUs * 15/16
 constexpr int64_t kBlockOverSplitMaxRowsDen = 16;
 
-// Split rows, two passes (rows too long for the one-pass shapes): 512 x 8
-// chunks, at most 64 workgroups per row (one exchange slot each, every
-// workgroup taking a stride of the row's chunks) and about 2048 per launch.
+// Split rows, two passes (rows too long for the one-pass shapes): the plan
+// names them in 512 x 8 chunks.  Both kernels run about four workgroups per CU
+// and group of rows (8 x 4194304: 2, 4 and 8 per CU within 3%; 1 x 33554432
+// slower by 20-70% with 8 and 16), at least one step of columns each.  A group
+// holds up to 256 MiB of x, so that the second kernel finds as much of it as
+// can be in the memory-side cache: 3 x 16777217 ran 112 us in one group and
+// 188 in three, 32 x 4194304 264 us in groups of 256 MiB, 277 of 128 and 300
+// of 64.
 constexpr int kSplitThreads = 512;
 constexpr int kSplitV = 8;
-constexpr int64_t kTwoPassWorkgroups = 2048;
+constexpr int64_t kLongGroupBytes = int64_t(256) << 20;
+constexpr int64_t kLongMaxRows = 64;
+constexpr int64_t kLongWorkgroupsPerCU = 4;
+static_assert(kLongMaxRows * kLongMaxEntries <= xch::kMaxRowsPerLaunch,
+              "a group's entries are those of one launch");
 
 // Store schedule of the one-pass split-row launches, in which every
 // workgroup is resident at once and takes one chunk: the stores wait until
@@ -419,8 +429,8 @@ const void* shape_fn(const Shape& s, bool stats_pass) {
     case SOFTMAX_KERNEL_SPLIT_ROW:
       if (s.two_pass) {
         if (s.threads != kSplitThreads || s.v != kSplitV) return nullptr;
-        return stats_pass ? cast(&k_split_stats<kSplitThreads, kSplitV, VEC4, EM>)
-                          : cast(&k_split_apply<kSplitThreads, kSplitV, VEC4, EM>);
+        return stats_pass ? cast(&k_long_stats<kLongThreads, EM>)
+                          : cast(&k_long_apply<kLongThreads, EM>);
       }
       if (s.ph) {
         if constexpr (VEC4 && EM != kLogOut) {
@@ -671,6 +681,16 @@ bool requested_shape(const softmax_plan_t& want, const float* x, const float* y,
   return true;
 }
 
+// Workgroups per row of the two-pass kernels for a group of nb rows, and the
+// columns that each of them takes.
+int long_workgroups(int64_t nb, int64_t cols, const DeviceFacts& f, int64_t* chunk) {
+  const int64_t want = std::min({int64_t(kLongMaxEntries) * xch::kEntrySlots,
+                                 ceil_div(kLongWorkgroupsPerCU * f.cus, nb),
+                                 ceil_div(cols, int64_t(4) * kLongStrips * kLongThreads)});
+  *chunk = (ceil_div(cols, want) + 3) & ~int64_t(3);
+  return static_cast<int>(ceil_div(cols, *chunk));
+}
+
 // Everything a call launches: the shape, its grid, rows per launch, chunks,
 // the store delay in ns and in wall-clock ticks, and the exchange wait limit.
 struct Plan {
@@ -679,7 +699,6 @@ struct Plan {
   int64_t rows_per_launch = 0;
   int64_t launches = 0;
   int64_t chunks = 1;
-  int64_t wpr = 1;  // two-pass: workgroups per row
   int64_t delay_ns = 0;       // the first launch's
   uint32_t delay_ticks = 0;
   bool delay_per_launch = false;  // the library's schedule: each launch by its own reads
@@ -888,11 +907,11 @@ int make_plan(const Shape& s, int64_t rows, int64_t cols, int em, int dev,
         one_wave = s.vec4;
         launch_read_bytes = std::min(rows, p.rows_per_launch) * cols * 4;
       } else {
-        // Workgroup w of a row takes chunks w, w + wpr, ...
-        p.wpr = std::min<int64_t>(p.chunks, xch::kEntrySlots);
-        p.rows_per_launch = std::min<int64_t>(std::max<int64_t>(1, kTwoPassWorkgroups / p.wpr),
-                                              xch::kMaxRowsPerLaunch);
-        p.grid = std::min(rows, p.rows_per_launch) * p.wpr;
+        p.rows_per_launch = std::min<int64_t>(std::max<int64_t>(1, kLongGroupBytes / (4 * cols)),
+                                              kLongMaxRows);
+        int64_t chunk = 0;
+        const int64_t nb = std::min(rows, p.rows_per_launch);
+        p.grid = nb * long_workgroups(nb, cols, f, &chunk);
         p.launches = 2 * ceil_div(rows, p.rows_per_launch);
       }
       break;
@@ -993,19 +1012,22 @@ hipError_t run_plan(const Plan& p, const float* x, float* y, const int64_t* labe
     return hipSuccess;
   }
   const void* fn_stats = kernel_fn(s, em, true);
-  int iwpr = static_cast<int>(p.wpr);
-  int64_t chunks = p.chunks;
   for (int64_t r0 = 0; r0 < rows; r0 += p.rows_per_launch) {
     const int64_t nb = std::min(p.rows_per_launch, rows - r0);
     const float* xb = x + r0 * cols;
     float* yb = y + r0 * cols;
-    XchArgs xa{f.scratch, exchange_key(yb, nonce), p.limit_ticks, 1u, entry_base(f, nb), 0u};
-    void* a1[] = {&xb, &xa, &cols, &iwpr, &chunks, &c};
-    hipError_t e = launch(fn_stats, nb * p.wpr, s.threads, a1, st);
+    int64_t chunk = 0;
+    int wpr = long_workgroups(nb, cols, f, &chunk);
+    int entries = static_cast<int>(ceil_div(wpr, xch::kEntrySlots));
+    XchArgs xa{f.scratch, exchange_key(yb, nonce), p.limit_ticks, 1u,
+               entry_base(f, nb * entries), 0u};
+    void* a1[] = {&xb, &xa, &cols, &wpr, &entries, &chunk};
+    hipError_t e = launch(fn_stats, nb * wpr, kLongThreads, a1, st);
     if (e != hipSuccess) return e;
+    int apr = wpr;
     XchArgs xb2{f.scratch, xa.key, p.limit_ticks, 0u, xa.base, 0u};  // find only
-    void* a2[] = {&xb, &yb, &xb2, &cols, &iwpr, &chunks, &c};
-    e = launch(fn, nb * p.wpr, s.threads, a2, st);
+    void* a2[] = {&xb, &yb, &xb2, &cols, &wpr, &entries, &apr, &chunk, &c};
+    e = launch(fn, nb * apr, kLongThreads, a2, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
