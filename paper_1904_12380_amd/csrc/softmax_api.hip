@@ -47,6 +47,35 @@ constexpr int64_t kWaveRowMaxCols = 4096;
 constexpr int64_t kWaveRowMaxColsScalar = 2048;
 constexpr int64_t kBlockRowMaxCols = 32768;
 constexpr int kBlockThreads = 1024;
+// One workgroup of 256 threads per row, with as many strips per lane as the
+// row needs (the wavefront and the 1024-thread kernels round them up to a
+// power of two and keep at most two rows of 1024 threads on a CU): rows of
+// 1088 to 4096 columns, probability rows up to 10240 (logs, which keep their
+// logits too, to 5120), and rows of 16381 to 24576 columns, which the split
+// kernel cuts into three chunks.  16-byte aligned x and y, whole strips or
+// with the row phase.  Measured at 2 to 256 MiB against those kernels:
+//  * 2049 x 64 MiB 28.1 -> 24.6 us, 3001 x 2 MiB 7.1 -> 3.9, 4096 x 8 MiB
+//    6.1 -> 4.8, 5000 x 64 MiB 28.4 -> 25.2, 1801 x 8 MiB 6.9 -> 5.4,
+//    8192 x 24 MiB 1.35 times faster, 18001 x 256 MiB 116 -> 100;
+//  * from 1025 to 1087 columns it lost up to 5% at 64 MiB, past 10240 up to
+//    10% from 128 MiB on (14000: 47.4 against 51.7 us) and 17% on few ragged
+//    rows, logs past 5120 up to 22% on few rows (14000 x 2 MiB 4.8 against
+//    6.1);
+//  * with between about one and two rounds of its resident workgroups (8 per
+//    CU) its last round is part empty while the wavefront kernel still runs
+//    one: whole strips of up to 4096 columns lost up to 18% there and keep the
+//    wavefront kernel (2048 columns at 8 to 22 rows per CU, 3072 at 6 to 17,
+//    4096 at 5 to 13; ragged probability rows, 6% at 11 to 13);
+//  * from 16381 columns on, ragged rows gain from a third of a row per CU
+//    (18001 x 116 9.9 -> 8.7 us, x 3728 116 -> 100), whole strips with more
+//    rows than CUs and up to 8 per CU (24000 x 699 29.2 -> 26.0, 17000 x 308
+//    11.8 -> 10.8; 20000 x 3355 2% slower), ragged log rows from two per CU
+//    (18001 x 932 36.0 -> 26.8 us, 20001 x 262 2% slower).
+constexpr int kRowThreads = 256;
+constexpr int64_t kRowMinCols = 1088;
+constexpr int64_t kRowMaxCols = 10240;
+constexpr int64_t kRowMaxColsLog = 5120;
+constexpr int64_t kRowOverSplitMaxCols = 24576 - 3;  // with a phase: 24 strips
 // Probability and log rows longer than this take the one-pass split kernel
 // rather than one workgroup per row (measured with the dispatch sweep,
 // paper_1904_12380_amd/sweep.py).  Per 64 MiB of logits, 16384 columns ran
@@ -171,9 +200,8 @@ constexpr int64_t kSplitWidePadDen = 16;  // extra padding of at least cols / 16
 // columns (no empty part) 1-9% slower in one workgroup, and 16388 columns x
 // 255 rows 1.3% slower.  At the bounds: 46-81 rows ran 3-6% faster split,
 // 89-105 rows 5-7% faster in one workgroup; 243 and 256 rows of 20480
-// columns 1.5-2.5% faster split.  With more rows than CUs the split kernel
-// was level or faster except at 17408 and 18432 columns x 455-481 rows
-// (4.5% slower).
+// columns 1.5-2.5% faster split.  With more rows than CUs:
+// kRowOverSplitMaxCols.
 constexpr int64_t kBlockOverSplitMinRowsDen = 3;   // rows >= CUs / 3
 constexpr int64_t kBlockOverSplitMaxRowsNum = 15;  // rows <= CUs * 15/16
 constexpr int64_t kBlockOverSplitMaxRowsDen = 16;
@@ -373,6 +401,36 @@ const void* packed_mode(const Shape& s) {
   return s.vec4 ? packed_shape_fn<EM, true>(s) : packed_shape_fn<EM, false>(s);
 }
 
+// k_block_row instances of kRowThreads threads: V strips per lane, for the
+// row lengths that small_block_shape gives them.
+template <int EM, bool PH>
+const void* small_block_fn(int v) {
+  auto cast = [](auto f) { return reinterpret_cast<const void*>(f); };
+  switch (v) {
+    case 2: return cast(&k_block_row<kRowThreads, 2, true, EM, PH>);
+    case 3: return cast(&k_block_row<kRowThreads, 3, true, EM, PH>);
+    case 4: return cast(&k_block_row<kRowThreads, 4, true, EM, PH>);
+    case 5: return cast(&k_block_row<kRowThreads, 5, true, EM, PH>);
+    default: break;
+  }
+  if constexpr (EM != kLogOut) {
+    switch (v) {
+      case 6: return cast(&k_block_row<kRowThreads, 6, true, EM, PH>);
+      case 8: return cast(&k_block_row<kRowThreads, 8, true, EM, PH>);
+      case 10: return cast(&k_block_row<kRowThreads, 10, true, EM, PH>);
+      default: break;
+    }
+  }
+  if constexpr (EM != kLogOut || PH) {
+    switch (v) {
+      case 20: return cast(&k_block_row<kRowThreads, 20, true, EM, PH>);
+      case 24: return cast(&k_block_row<kRowThreads, 24, true, EM, PH>);
+      default: break;
+    }
+  }
+  return nullptr;
+}
+
 template <int EM, bool VEC4>
 const void* shape_fn(const Shape& s, bool stats_pass) {
   auto cast = [](auto f) { return reinterpret_cast<const void*>(f); };
@@ -410,6 +468,11 @@ const void* shape_fn(const Shape& s, bool stats_pass) {
         default: return nullptr;
       }
     case SOFTMAX_KERNEL_BLOCK_ROW:
+      if (s.threads == kRowThreads) {
+        if constexpr (VEC4)
+          return s.ph ? small_block_fn<EM, true>(s.v) : small_block_fn<EM, false>(s.v);
+        return nullptr;
+      }
       if (s.ph) {
         if constexpr (VEC4) {
           switch (s.v) {
@@ -746,6 +809,46 @@ int group_rows_steps(int64_t rows, int em, int dev, const DeviceFacts& f, Shape*
   return SOFTMAX_OK;
 }
 
+// One workgroup of kRowThreads threads per row where that is the fastest
+// (kRowMinCols and below it): fills in the shape and returns true.
+bool small_block_shape(const float* x, const float* y, int64_t rows, int64_t cols, int em,
+                       const DeviceFacts& f, Shape* out) {
+  if (!aligned16(x) || !aligned16(y) || em == kNllOut) return false;
+  const bool ph = cols % 4 != 0;
+  const bool log = em == kLogOut;
+  auto between = [&](int64_t lo, int64_t hi) { return rows > lo * f.cus && rows <= hi * f.cus; };
+  bool take = false;
+  if (cols < kRowMinCols) {
+    take = false;
+  } else if (cols <= kWaveRowMaxCols) {
+    take = ph                             ? log || !between(11, 13)
+           : cols <= kWaveRowMaxColsScalar ? !between(8, 22)
+           : cols <= 3072                  ? !between(6, 17)
+                                           : !between(5, 13);
+  } else if (cols <= kRowMaxCols) {
+    take = !log || cols <= kRowMaxColsLog;
+  } else if (cols > kSplitMinColsProb && cols <= kRowOverSplitMaxCols) {
+    take = log  ? ph && rows >= 2 * f.cus
+           : ph ? 3 * rows >= f.cus
+                : rows > f.cus && rows <= 8 * f.cus;
+  }
+  if (!take) return false;
+  const int64_t strips = ceil_div(cols + (ph ? 3 : 0), int64_t(4) * kRowThreads);
+  Shape s;
+  s.kernel = SOFTMAX_KERNEL_BLOCK_ROW;
+  s.vec4 = true;
+  s.ph = ph;
+  s.threads = kRowThreads;
+  s.v = strips <= 6    ? static_cast<int>(std::max<int64_t>(2, strips))
+        : strips <= 8  ? 8
+        : strips <= 10 ? 10
+        : strips <= 20 ? 20
+                       : 24;
+  if (kernel_fn(s, em) == nullptr) return false;
+  *out = s;
+  return true;
+}
+
 // The shape of rows of more than kPackedMaxCols columns read with 32-bit
 // access.
 Shape scalar_row_shape(int64_t cols) {
@@ -775,6 +878,10 @@ Shape scalar_row_shape(int64_t cols) {
 int library_shape(const float* x, const float* y, int64_t rows, int64_t cols, int em, int dev,
                   const DeviceFacts& f, Shape* out) {
   Shape s = default_shape(x, y, cols, em);
+  if (small_block_shape(x, y, rows, cols, em, f, &s)) {
+    *out = s;
+    return SOFTMAX_OK;
+  }
   if ((s.kernel == SOFTMAX_KERNEL_PACKED && s.g >= 8 &&
        (rows <= f.cus * (cols > kPackedWideCols ? kPackedMinRowsPerCUWide : kPackedMinRowsPerCU) ||
         (em == kLogOut && cols > kLogPackedMaxCols))) ||

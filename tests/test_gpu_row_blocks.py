@@ -1,0 +1,78 @@
+"""GPU parity of the 256-thread row kernel at the edges of its ranges: each
+count of strips per lane full, with one column more and with a start phase,
+row counts on both sides of the changes to the other kernels (taken from the
+device's compute units), every output, in place and between canaries.  Bars
+are the header's, against the float64 oracle.
+"""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1904_12380_amd as sm
+import workloads
+
+pytestmark = pytest.mark.gpu
+NEG_INF = float("-inf")
+
+
+def _cus():
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def _check(rows, cols):
+    x = workloads.random_logits(rows, cols, seed=rows * 7 + cols, kind="clip_heavy", scale=30.0)
+    x[0, cols - 1] = -np.inf
+    x[rows - 1, cols // 2] = np.nan
+    if rows > 2:
+        x[1, :] = -np.inf
+    n = rows * cols
+    buf = torch.full((n + 8,), 9.0, device="cuda:0")
+    yt = buf[4:4 + n].view(rows, cols)
+    xt = torch.from_numpy(x).to("cuda:0")
+    d = np.minimum(np.abs(x.astype(np.float64) - x.max(1, keepdims=True)), 64.0)
+    for name, lo in (("fwd", -64.0), ("clip", NEG_INF), ("approx", -64.0), ("log", NEG_INF),
+                     ("inplace", -64.0)):
+        want = oracle.log_softmax_clipped(x, lo) if name == "log" else oracle.softmax_clipped(x, lo)
+        if name == "approx":
+            sm.softmax_fwd_approx(xt, lo, out=yt)
+        elif name == "log":
+            sm.softmax_log_fwd(xt, lo, out=yt)
+        elif name == "inplace":
+            yt.copy_(xt)
+            sm.softmax_fwd(yt, out=yt)
+        else:
+            sm.softmax_fwd_clip(xt, lo, out=yt)
+        torch.cuda.synchronize()
+        got = yt.cpu().numpy().astype(np.float64)
+        assert np.array_equal(np.isnan(got), np.isnan(want)), name
+        assert np.array_equal(np.isneginf(got), np.isneginf(want)), name
+        fin = np.isfinite(want)
+        w = want[fin]
+        tol = (2e-6 + 2.5e-7 * (np.abs(w) + math.log(cols)) if name == "log" else
+               (2e-6 + 1.5e-7 * d[fin]) * w if name == "approx" else 4e-6 * w + 2.0 ** -148)
+        assert np.all(np.abs(got[fin] - w) <= tol), (name, rows, cols)
+        edge = torch.cat([buf[:4], buf[4 + n:]]).cpu().numpy()
+        assert np.all(edge == np.float32(9.0)), (name, "written outside the output")
+
+
+@pytest.mark.parametrize("cols", [1087, 1088, 2045, 2046, 2048, 2049, 3069, 3070, 3072, 3073,
+                                  4093, 4094, 4096, 4097, 5117, 5118, 5120, 5121, 6142, 8189,
+                                  8192, 8193, 10237, 10240, 10241])
+def test_strips(cols):
+    print(f"[row-blocks] {cols}", flush=True)
+    _check(5, cols)
+    _check(2, cols)
+
+
+@pytest.mark.parametrize("cols,num,den", [(1500, 8, 1), (2051, 11, 1), (2060, 6, 1),
+                                          (4000, 5, 1), (2049, 13, 1), (16384, 1, 1),
+                                          (20480, 1, 1), (20481, 1, 3), (24573, 1, 3),
+                                          (24572, 1, 1), (16385, 1, 3)])
+def test_row_counts(cols, num, den):
+    rows = _cus() * num // den
+    for r in (rows, rows + 1):
+        print(f"[row-blocks] {r}x{cols}", flush=True)
+        _check(r, cols)
