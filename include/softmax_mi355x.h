@@ -69,15 +69,16 @@ extern "C" {
 #define SOFTMAX_KERNEL_WAVE_ROW 2  /* cols <= 4096: one wavefront per row
                                       (rows that are not whole 16-byte
                                       strips: 128-bit access in the aligned
-                                      strips around the row above 2048) */
-#define SOFTMAX_KERNEL_BLOCK_ROW 3 /* cols <= 16380: one workgroup per
-                                      row; also
-                                      probability rows of 16385 to 24575
-                                      columns in whole strips when the
-                                      device has between 15/16 and 3 times
-                                      as many compute units as there are
-                                      rows (the split grid's third chunk
-                                      would be partly empty) */
+                                      strips around the row above 2048);
+                                      from 1088 columns on where BLOCK_ROW
+                                      is slower for the number of rows */
+#define SOFTMAX_KERNEL_BLOCK_ROW 3 /* cols <= 16380: one workgroup per row
+                                      (256 threads from 1088 to 10240
+                                      columns, log outputs to 5120, else
+                                      1024); also rows of 16381 to 24576
+                                      columns, by their number and the
+                                      device, where the split grid's third
+                                      chunk would be partly empty */
 #define SOFTMAX_KERNEL_SPLIT_ROW 4 /* longer rows: several workgroups per row
                                       (chunks aligned to the row's phase for
                                       rows that are not whole strips) */

@@ -371,7 +371,7 @@ __device__ __forceinline__ void attn_compute(const float* lk_s, const float* lv_
 // item's copies in flight beside another's matrix ops, one wavefront of
 // each team per SIMD.  Every wavefront passes the same barriers: one after
 // the first copy, one per phase.  The team that copies has raised priority
-// while it issues, as in k_attention_lds.
+// while it issues.
 template <int NKT, bool WIDE, int DC>
 __global__ __launch_bounds__(512) void k_attention_pp(
     const float* q, const float* k, const float* v, float* o, int64_t batch, int lq, int lk,
