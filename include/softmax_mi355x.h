@@ -370,6 +370,8 @@ SOFTMAX_API int softmax_plan(const float* x, const float* y, int64_t rows, int64
  *                   the library itself picks for rows that are not whole
  *                   strips: wave or block rows of 2049 to 8189 columns,
  *                   split rows whose phase adds no chunk) or 1;
+ *   block_threads   one workgroup per row: 256 for the 256-thread kernel on
+ *       rows that softmax_plan() gives it, anything else for 1024;
  *   block_threads, elems_per_lane   split rows only: 256 x 32 (chunks of
  *                   8192 columns), 512 x 32 (16384) or, with vec_width 4,
  *                   512 x 64 (32768); rows of more than 64 chunks take the

@@ -684,8 +684,33 @@ Shape default_shape(const float* x, const float* y, int64_t cols, int em) {
   return s;
 }
 
-// A caller's shape (softmax_fwd_planned): the family, access width and, for
-// split rows, the chunk shape; everything else is derived.  Returns false
+// One workgroup of kRowThreads threads per row, with as many strips per lane
+// as the row needs: false where the library never takes such rows.
+bool row_block_shape(const float* x, const float* y, int64_t cols, int em, Shape* out) {
+  if (!aligned16(x) || !aligned16(y) || cols < kRowMinCols || cols > kRowOverSplitMaxCols + 3 ||
+      (cols > kRowMaxCols && cols <= kSplitMinColsProb))
+    return false;
+  const bool ph = cols % 4 != 0;
+  const int64_t strips = ceil_div(cols + (ph ? 3 : 0), int64_t(4) * kRowThreads);
+  if (strips > 24) return false;
+  Shape s;
+  s.kernel = SOFTMAX_KERNEL_BLOCK_ROW;
+  s.vec4 = true;
+  s.ph = ph;
+  s.threads = kRowThreads;
+  s.v = strips <= 6    ? static_cast<int>(std::max<int64_t>(2, strips))
+        : strips <= 8  ? 8
+        : strips <= 10 ? 10
+        : strips <= 20 ? 20
+                       : 24;
+  if (kernel_fn(s, em) == nullptr) return false;
+  *out = s;
+  return true;
+}
+
+// A caller's shape (softmax_fwd_planned): the family, access width, for
+// split rows the chunk shape and for one workgroup per row its threads (256,
+// where the library has that kernel for the row); everything else is derived.  Returns false
 // when the shape is not one the library has or cannot take these rows.
 bool requested_shape(const softmax_plan_t& want, const float* x, const float* y, int64_t cols,
                      int em, Shape* out) {
@@ -708,6 +733,9 @@ bool requested_shape(const softmax_plan_t& want, const float* x, const float* y,
     *out = s;
     return true;
   }
+  if (s.vec4 && s.kernel == SOFTMAX_KERNEL_BLOCK_ROW && want.block_threads == kRowThreads &&
+      row_block_shape(x, y, cols, em, out))
+    return true;
   if (s.vec4 && row_kernel && phase_rows(x, y, cols)) {
     const int64_t span = cols + 3;
     if (span > (s.kernel == SOFTMAX_KERNEL_WAVE_ROW ? kWaveRowMaxCols : kSplitMinColsProb))
@@ -838,7 +866,6 @@ int group_rows_steps(int64_t rows, int em, int dev, const DeviceFacts& f, Shape*
 // (kRowMinCols and below it): fills in the shape and returns true.
 bool small_block_shape(const float* x, const float* y, int64_t rows, int64_t cols, int em,
                        const DeviceFacts& f, Shape* out) {
-  if (!aligned16(x) || !aligned16(y) || em == kNllOut) return false;
   const bool ph = cols % 4 != 0;
   const bool log = em == kLogOut;
   auto between = [&](int64_t lo, int64_t hi) { return rows > lo * f.cus && rows <= hi * f.cus; };
@@ -858,20 +885,7 @@ bool small_block_shape(const float* x, const float* y, int64_t rows, int64_t col
                 : rows > f.cus && rows <= 8 * f.cus;
   }
   if (!take) return false;
-  const int64_t strips = ceil_div(cols + (ph ? 3 : 0), int64_t(4) * kRowThreads);
-  Shape s;
-  s.kernel = SOFTMAX_KERNEL_BLOCK_ROW;
-  s.vec4 = true;
-  s.ph = ph;
-  s.threads = kRowThreads;
-  s.v = strips <= 6    ? static_cast<int>(std::max<int64_t>(2, strips))
-        : strips <= 8  ? 8
-        : strips <= 10 ? 10
-        : strips <= 20 ? 20
-                       : 24;
-  if (kernel_fn(s, em) == nullptr) return false;
-  *out = s;
-  return true;
+  return row_block_shape(x, y, cols, em, out);
 }
 
 // The shape of rows of more than kPackedMaxCols columns read with 32-bit

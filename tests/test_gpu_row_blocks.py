@@ -76,3 +76,17 @@ def test_row_counts(cols, num, den):
     for r in (rows, rows + 1):
         print(f"[row-blocks] {r}x{cols}", flush=True)
         _check(r, cols)
+
+
+@pytest.mark.parametrize("rows,cols", [(300, 1501), (300, 1500), (300, 3001), (700, 5000),
+                                       (9, 10237), (600, 18001), (400, 17000), (300, 24573),
+                                       (9, 12001), (300, 1087), (5000, 130)])
+def test_a_plan_runs_as_planned(rows, cols):
+    """softmax_fwd_planned takes what softmax_plan reports and runs the same
+    kernel: the same bits."""
+    print(f"[row-blocks] plan {rows}x{cols}", flush=True)
+    x = torch.randn(rows, cols, device="cuda:0")
+    y = torch.empty_like(x)
+    plan = sm.softmax_plan(rows, cols, x.data_ptr(), y.data_ptr())
+    sm.softmax_fwd_planned(x, plan, out=y)
+    assert torch.equal(y, sm.softmax_fwd(x))
