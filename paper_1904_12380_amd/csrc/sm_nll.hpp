@@ -61,7 +61,7 @@ struct NllSum {
     float t[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) t[i] = nll_term(v[i], ref);
-    s = s * nll_term(m, ref) + tree_sum(t);
+    s = s * nll_rescale(m, ref) + tree_sum(t);  // partial sums keep the accurate exponential
     m = m_new;
   }
 };
