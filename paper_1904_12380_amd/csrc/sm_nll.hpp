@@ -38,10 +38,12 @@ __device__ __forceinline__ float nll_term(float x, float m) {
   return __builtin_amdgcn_exp2f((x - m) * 0x1.715476p+0f);
 }
 
-// exp(d) for d <= 0 within 1.5 ulp (0 below about -87), for rescaling
-// partial sums: the argument in binary64 as in exp_shift_clip.
+// exp(m - m_new) for m <= m_new within 1.5 ulp (0 below about -87), for
+// rescaling partial sums: the difference and the argument in binary64 as in
+// exp_shift_clip (a difference rounded to fp32 is off by up to |d| 2^-24, which
+// the exponential turns into that relative error of the sum).
 __device__ __forceinline__ float nll_rescale(float m, float m_new) {
-  const double d = static_cast<double>(fmaxf(m - m_new, -126.0f));
+  const double d = fmax(static_cast<double>(m) - static_cast<double>(m_new), -126.0);
   const float th = static_cast<float>(d * kLog2e);
   const double r = __builtin_fma(static_cast<double>(th), -kLn2, d);
   const float e0 = __builtin_amdgcn_exp2f(th);
