@@ -31,10 +31,7 @@ namespace smx {
 // (log outputs: the fast one, as their other row sums).  Unclipped, as
 // NllSum: a clipped term is under 1.5e-21 of a row sum.
 template <int MODE>
-struct LongSum {
-  float m = kNegInf;
-  float s = 0.0f;
-
+struct LongSum : RunningSum {
   __device__ __forceinline__ static float term(float x, RowShift rs) {
     if constexpr (MODE == kLogOut || MODE == kExpFast)
       return nll_term(x, rs.m);
@@ -47,13 +44,12 @@ struct LongSum {
   }
   template <int N>
   __device__ __forceinline__ void add(const float (&v)[N]) {
-    const float m_new = fmaxf(m, array_max(v));
-    const RowShift rs = shift(m_new);
+    grow(fmaxf(m, array_max(v)));
+    const RowShift rs = shift(m);
     float t[8];
 #pragma unroll
     for (int i = 0; i < N; ++i) t[i % 8] = i < 8 ? term(v[i], rs) : t[i % 8] + term(v[i], rs);
-    s = s * nll_rescale(m, rs.m) + tree_sum(t);
-    m = m_new;
+    s += static_cast<double>(tree_sum(t));
   }
 };
 
@@ -75,8 +71,7 @@ __global__ __launch_bounds__(NT) void k_long_stats(const float* x, XchArgs xa, i
   const LongSum<MODE> own =
       stream_sum<NT, kLongStrips, false, LongSum<MODE>>(x + lrow * cols + c0, n, tid, [] {});
   const float m = block_max<NT / 64>(own.m, red_max);
-  const float s =
-      block_sum<NT / 64>(own.s * nll_rescale(own.m, m == kNegInf ? 0.0f : m), red_sum);
+  const float s = block_sum<NT / 64>(own.share(m), red_sum);
   if (tid < 64) {
     uint64_t* entry =
         wave_entry(xa, lrow * entries + w / xch::kEntrySlots, t0 + xa.limit_ticks);

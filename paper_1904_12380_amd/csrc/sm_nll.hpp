@@ -50,21 +50,66 @@ __device__ __forceinline__ float nll_rescale(float m, float m_new) {
   return __builtin_fmaf(e0, static_cast<float>(r), e0);
 }
 
-// A lane's running max and sum of exp(x - m); a lane that has seen only
-// -inf has m = -inf, s = 0.
-struct NllSum {
-  float m = kNegInf;
-  float s = 0.0f;
+// c in scalar registers, formed where it is used: the compiler otherwise keeps
+// the constants below in vector registers across the loops around them (10
+// more, one wavefront per SIMD less).
+__device__ __forceinline__ double scalar_here(double c) {
+  asm volatile("" : "+s"(c));
+  return c;
+}
 
+// exp(d) for -126 <= d <= 0 in binary64, within 1e-11 relative:
+// d = n ln 2 + 16 q with |q| <= ln 2 / 32, e^q by its Taylor series to q^5
+// (truncated at q^6 / 720 < 2e-13), squared four times, times 2^n.
+__device__ __forceinline__ double exp_rescale(double d) {
+  const double n = __builtin_rint(d * scalar_here(kLog2e));
+  const double q = __builtin_fma(n, scalar_here(-kLn2), d) * 0x1p-4;
+  double e = __builtin_fma(q, scalar_here(1.0 / 120), scalar_here(1.0 / 24));
+  e = __builtin_fma(q, e, scalar_here(1.0 / 6));
+  e = __builtin_fma(q, e, 0.5);
+  e = __builtin_fma(q, e, 1.0);
+  e = __builtin_fma(q, e, 1.0);
+  e *= e;
+  e *= e;
+  e *= e;
+  e *= e;
+  return __builtin_ldexp(e, static_cast<int>(n));
+}
+
+// A lane's running max m and sum s of exp(x - m); a lane that has seen only
+// -inf has m = -inf, s = 0.  A lane takes one step after another, thousands on
+// a long row that is not split, so the sum and its rescaling are binary64: in
+// fp32, steps that look alike round alike, and 384 x 4194304 (1024 steps) was
+// off by 1.5e-5 on logits that repeat with the step and 1.3e-5 on logits that
+// rise steadily, above the stated bound.  The exponential of a rescaling runs
+// only where a lane's max has grown.
+struct RunningSum {
+  float m = kNegInf;
+  double s = 0.0;
+
+  // Brings m to m_new, the max with the next step's logits (called before
+  // their exponentials: fewer registers).
+  __device__ __forceinline__ void grow(float m_new) {
+    if (m < m_new)
+      s *= exp_rescale(fmax(static_cast<double>(m) - static_cast<double>(m_new), -126.0));
+    m = m_new;
+  }
+  // The sum against the row's max m_row.
+  __device__ __forceinline__ float share(float m_row) const {
+    return static_cast<float>(s) * nll_rescale(m, m_row == kNegInf ? 0.0f : m_row);
+  }
+};
+
+struct NllSum : RunningSum {
   template <int N>
   __device__ __forceinline__ void add(const float (&v)[N]) {
-    const float m_new = fmaxf(m, array_max(v));
-    const float ref = m_new == kNegInf ? 0.0f : m_new;
-    float t[N];
+    grow(fmaxf(m, array_max(v)));
+    const float ref = m == kNegInf ? 0.0f : m;
+    float t[8];
 #pragma unroll
-    for (int i = 0; i < N; ++i) t[i] = nll_term(v[i], ref);
-    s = s * nll_rescale(m, ref) + tree_sum(t);  // partial sums keep the accurate exponential
-    m = m_new;
+    for (int i = 0; i < N; ++i)
+      t[i % 8] = i < 8 ? nll_term(v[i], ref) : t[i % 8] + nll_term(v[i], ref);
+    s += static_cast<double>(tree_sum(t));
   }
 };
 
@@ -92,7 +137,7 @@ __device__ __forceinline__ Sum stream_sum(const float* p, int64_t n, int t, F af
   if (t >= head && t - head < tail) edge = ps[4 * strips + t - head];
   Sum acc;
   acc.m = fmaxf(acc.m, edge);
-  acc.s = edge == kNegInf ? 0.0f : 1.0f + (edge - edge);  // NaN for a NaN or +inf edge
+  acc.s = edge == kNegInf ? 0.0 : 1.0 + (edge - edge);  // NaN for a NaN or +inf edge
   f32x4 q[U];
   auto ld = [](const float* a) {
     return NTL ? ld_stream(a) : *reinterpret_cast<const f32x4*>(a);
@@ -138,18 +183,15 @@ __device__ __forceinline__ NllSum nll_stream(const float* p, int64_t n, int t, F
 template <int NT>
 __device__ __forceinline__ float2 nll_combine(NllSum a, float* red_max, float* red_sum) {
   const float m = block_max<NT / 64>(a.m, red_max);
-  const float s =
-      block_sum<NT / 64>(a.s * nll_rescale(a.m, m == kNegInf ? 0.0f : m), red_sum);
-  return make_float2(m, s);
+  return make_float2(m, block_sum<NT / 64>(a.share(m), red_sum));
 }
 
 // One wavefront (NT = 64, four rows per workgroup) or one workgroup of NT
 // threads per row.
 template <int NT, int U>
-__global__ __launch_bounds__(NT < 256 ? 256 : NT) void k_nll_rows(const float* x,
-                                                                  const int64_t* labels,
-                                                                  float* y, int64_t rows,
-                                                                  int64_t cols, Clip clip) {
+__global__ __launch_bounds__(NT < 256 ? 256 : NT)
+    __attribute__((amdgpu_waves_per_eu(NT == 64 ? 7 : 8))) void k_nll_rows(
+        const float* x, const int64_t* labels, float* y, int64_t rows, int64_t cols, Clip clip) {
   constexpr int kRows = NT == 64 ? 4 : 1;  // rows per workgroup
   __shared__ float red_max[NT / 64];
   __shared__ float red_sum[NT / 64];
