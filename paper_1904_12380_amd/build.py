@@ -3,7 +3,8 @@
     python -m paper_1904_12380_amd.build
 
 Produces paper_1904_12380_amd/lib/libsoftmax_mi355x.so from csrc/ with
-hipcc.  Compiles every time it is called.
+hipcc and, where the tests are there, the library that lets them run kernels
+on an exchange table of their own.  Compiles every time it is called.
 """
 from __future__ import annotations
 
@@ -18,6 +19,8 @@ CSRC = os.path.join(PKG, "csrc")
 LIBDIR = os.path.join(PKG, "lib")
 LIB = os.path.join(LIBDIR, "libsoftmax_mi355x.so")
 SOURCES = [os.path.join(CSRC, "softmax_api.hip"), os.path.join(CSRC, "attention_api.hip")]
+PROBE_SOURCE = os.path.join(ROOT, "tests", "native", "long_rows_probe.hip")
+PROBE_LIB = os.path.join(ROOT, "tests", "native", "liblong_rows_probe.so")
 
 ARCH = "gfx950"
 HIPCC_FLAGS = [
@@ -68,12 +71,19 @@ def build(verbose: bool = False) -> str:
     compile_flags = [f for f in HIPCC_FLAGS if f != "-shared"]
     procs = [_run([hipcc(), *compile_flags, "-I", os.path.join(ROOT, "include"), "-c", src,
                    "-o", obj], verbose) for src, obj in zip(SOURCES, objs)]
+    probe = None
+    if os.path.exists(PROBE_SOURCE):
+        probe = _run([hipcc(), *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), PROBE_SOURCE,
+                      "-o", PROBE_LIB + tag], verbose)
     try:
         for proc in procs:
             _finish(proc, verbose)
         tmp = LIB + tag
         _finish(_run([hipcc(), *HIPCC_FLAGS, *objs, "-o", tmp], verbose), verbose)
         os.replace(tmp, LIB)
+        if probe is not None:
+            _finish(probe, verbose)
+            os.replace(PROBE_LIB + tag, PROBE_LIB)
     finally:
         for obj in objs:
             if os.path.exists(obj):

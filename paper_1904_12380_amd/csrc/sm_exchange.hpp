@@ -27,7 +27,8 @@
 //
 // Every wait is bounded by the wall clock.  A workgroup that gives up
 // counts itself in a give-up counter (readable from the host), writes NaN
-// for its outputs, and leaves the entry alone.
+// for its outputs, and leaves the entry alone.  A row of several entries
+// (the two-pass kernels) that lacks one gives back those it claimed.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -80,6 +80,14 @@ __global__ __launch_bounds__(NT) void k_long_stats(const float* x, XchArgs xa, i
   }
 }
 
+// Puts entry `e` of the launch back to rest, its first `slots` slots (at most
+// kEntrySlots) zeroed; by one wavefront, once nothing reads the entry.
+__device__ __forceinline__ void release_long_entry(const XchArgs& xa, int e, int slots) {
+  uint64_t* const entry = find_entry(xa, e);
+  if (__lane_id() < slots) xch::st_agent(&entry_slots(entry)[__lane_id()], 0ull);
+  if (__lane_id() == 0) release_entry(entry);
+}
+
 template <int NT, int MODE>
 __global__ __launch_bounds__(NT) void k_long_apply(const float* x, float* y, XchArgs xa,
                                                    int64_t cols, int wpr, int entries, int apr,
@@ -193,11 +201,18 @@ __global__ __launch_bounds__(NT) void k_long_apply(const float* x, float* y, Xch
     }
     last = __builtin_amdgcn_readfirstlane(last);
     if (last) {
-      for (int k = 0; k < entries; ++k) {
-        uint64_t* const e = find_entry(xa, lrow * entries + k);
-        if (k * xch::kEntrySlots + lane < wpr) xch::st_agent(&entry_slots(e)[lane], 0ull);
-        if (tid == 0) release_entry(e);
-      }
+      for (int k = 0; k < entries; ++k)
+        release_long_entry(xa, lrow * entries + k, wpr - k * xch::kEntrySlots);
+    }
+  } else if (tid < 64 && w == 0) {
+    // The row lacks an entry, which k_long_stats could not join in time: all of
+    // the row's workgroups see that (the entry cannot gain the row's tag any
+    // more), so none of them reads a slot or counts itself out, and the row's
+    // first one gives back the entries that the row did claim.
+    for (int k = 0; k < entries; ++k) {
+      const int e = lrow * entries + k;
+      if (xch::ld_agent(find_entry(xa, e)) == row_tag(xa, e))
+        release_long_entry(xa, e, wpr - k * xch::kEntrySlots);
     }
   }
 }
