@@ -206,24 +206,6 @@ constexpr int64_t kBlockOverSplitMinRowsDen = 3;   // rows >= CUs / 3
 constexpr int64_t kBlockOverSplitMaxRowsNum = 15;  // rows <= CUs * 15/16
 constexpr int64_t kBlockOverSplitMaxRowsDen = 16;
 
-// One-pass launches hold the rows whose workgroups are resident at once, so
-// that the store schedule can keep reads and writes apart.  A rest of at most
-// kSplitJoinPct percent of such a launch (ragged rows, whose launches gain less
-// from the schedule: kSplitJoinPctPhase) joins the last full one instead (rows
-// of up to 8 chunks, fewer than three launches): its workgroups start as the first ones
-// end, without a launch and a ramp of their own, and without the schedule.  A
-// row's workgroups still have consecutive IDs, so the lowest unfinished row has
-// its workgroups as soon as that many slots are free.  Measured: 335 x 50001
-// (292 + 43 rows) 31.4 -> 28.8 us, 599 x 28001 (512 + 87) 31.5 -> 29.1,
-// 471 x 40000 (62 over) 31.0 -> 29.7, 674 x 28001 (162 over) 33.5 -> 31.4;
-// 640 x 32768 (128 over) 5% slower.  With 32-bit access, which has no schedule,
-// up to kMaxRowsPerLaunch rows of up to 32 chunks go in one launch: log rows
-// 83 x 400001 1.14 times faster, 256 x 131071 1.08; 36 x 1000001 (62 chunks)
-// 6% slower.
-constexpr int64_t kSplitJoinPct = 20;
-constexpr int64_t kSplitJoinPctPhase = 35;
-constexpr int64_t kSplitOneLaunchMaxChunks = 32;
-
 // Split rows, two passes (rows too long for the one-pass shapes): the plan
 // names them in 512 x 8 chunks.  Both kernels run about four workgroups per CU
 // and group of rows (8 x 4194304: 2, 4 and 8 per CU within 3%; 1 x 33554432
@@ -806,19 +788,12 @@ struct Plan {
   Shape shape;
   int64_t grid = 0;
   int64_t rows_per_launch = 0;
-  int64_t resident_rows = 0;  // one-pass: rows whose workgroups are resident at once
-  int64_t join_rows = 0;      // one-pass: a rest of at most so many rows joins a launch
   int64_t launches = 0;
   int64_t chunks = 1;
   int64_t delay_ns = 0;       // the first launch's
   uint32_t delay_ticks = 0;
   bool delay_per_launch = false;  // the library's schedule: each launch by its own reads
   uint32_t limit_ticks = 0;
-
-  // One-pass split rows: the rows of the next launch when `left` are left.
-  int64_t rows_of_launch(int64_t left) const {
-    return left <= rows_per_launch + join_rows ? left : rows_per_launch;
-  }
 };
 
 uint32_t ns_to_ticks(int64_t ns, const DeviceFacts& f) {
@@ -1045,25 +1020,13 @@ int make_plan(const Shape& s, int64_t rows, int64_t cols, int em, int dev,
         // Whole rows per launch, every workgroup of a launch resident at
         // once.
         if (p.chunks > resident || p.chunks > kOnePassMaxChunks) return SOFTMAX_ERR_INVALID_ARG;
-        const int64_t fit =
-            std::min(resident / p.chunks, int64_t(xch::kMaxRowsPerLaunch));
-        p.rows_per_launch = s.vec4 || p.chunks > kSplitOneLaunchMaxChunks
-                                ? fit
-                                : int64_t(xch::kMaxRowsPerLaunch);
-        // A short rest joins the last full launch (kSplitJoinNum).
-        if (s.vec4 && p.chunks <= kSmallChunkMaxChunks && rows < 3 * fit)
-          p.join_rows = std::min(fit * (s.ph ? kSplitJoinPctPhase : kSplitJoinPct) / 100,
-                                 xch::kMaxRowsPerLaunch - fit);
-        p.resident_rows = fit;
-        int64_t rest = rows;
-        p.launches = 0;
-        for (; rest > 0; ++p.launches) rest -= p.rows_of_launch(rest);
-        p.grid = p.rows_of_launch(rows) * p.chunks;
+        p.rows_per_launch = std::min(resident / p.chunks, int64_t(xch::kMaxRowsPerLaunch));
+        p.grid = std::min(rows, p.rows_per_launch) * p.chunks;
+        p.launches = ceil_div(rows, p.rows_per_launch);
         // The store schedule pays with 128-bit access; with 32-bit access
         // (rows of 16383 and 32765 columns) it measured 0.1-0.4 us slower.
         one_wave = s.vec4;
-        launch_read_bytes =
-            p.rows_of_launch(rows) <= fit ? p.rows_of_launch(rows) * cols * 4 : 0;
+        launch_read_bytes = std::min(rows, p.rows_per_launch) * cols * 4;
       } else {
         p.rows_per_launch = std::min<int64_t>(std::max<int64_t>(1, kLongGroupBytes / (4 * cols)),
                                               kLongMaxRows);
@@ -1150,16 +1113,15 @@ hipError_t run_plan(const Plan& p, const float* x, float* y, const int64_t* labe
   const uint32_t nonce = g_nonce.fetch_add(1, std::memory_order_relaxed);
   if (!s.two_pass) {
     int ichunks = static_cast<int>(p.chunks);
-    int64_t nb = 0;
-    for (int64_t r0 = 0; r0 < rows; r0 += nb) {
-      nb = p.rows_of_launch(rows - r0);
+    for (int64_t r0 = 0; r0 < rows; r0 += p.rows_per_launch) {
+      const int64_t nb = std::min(p.rows_per_launch, rows - r0);
       const float* xb = x + r0 * cols;
       float* yb = y + r0 * cols;
       // A short last launch waits only as long as its own reads take: with
       // the first launch's delay, 10 rows of 40000 columns after 409 waited
       // 8.9 us before storing.
       if (p.delay_per_launch) {
-        const int64_t ns = nb <= p.resident_rows ? store_delay_ns(nb * cols * 4) : 0;
+        const int64_t ns = store_delay_ns(nb * cols * 4);
         delay = ns > 0 ? ns_to_ticks(ns, f) : 0;
       }
       XchArgs xa{f.scratch, exchange_key(yb, nonce), p.limit_ticks, 1u,  // join
