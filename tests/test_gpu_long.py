@@ -1,7 +1,8 @@
 """GPU parity of the two streaming passes over rows too long for one pass:
-one row and several, several groups' worth of exchange entries, ragged ends,
-x and y at the same and at different phases, in place, every output, and
-non-finite rows.  Bars are the header's, against the float64 oracle.
+one row and several, rows of one to 16 exchange entries, more rows than one
+group of launches takes, ragged ends, x and y at the same and at different
+phases, in place, every output, and non-finite rows.  Bars are the header's,
+against the float64 oracle.
 """
 import math
 
@@ -31,7 +32,8 @@ def _rest(buf, off, n, fill):
 @pytest.mark.parametrize("rows,cols,xo,yo", [(1, 2097153, 4, 4), (1, 2097160, 4, 4),
                                              (3, 2097155, 1, 1), (2, 2500003, 1, 4),
                                              (2, 2100000, 3, 1), (5, 2097156, 0, 2),
-                                             (1, 4194304, 0, 0)])
+                                             (1, 4194304, 0, 0), (1, 8388611, 1, 1),
+                                             (1, 8388611, 4, 3)])
 def test_rows(rows, cols, xo, yo):
     print(f"[long] {rows}x{cols}+{xo}+{yo}", flush=True)
     x = workloads.random_logits(rows, cols, seed=cols + rows, kind="clip_heavy")
@@ -62,6 +64,30 @@ def test_rows(rows, cols, xo, yo):
     sm.softmax_fwd(xt, out=xt)  # in place
     torch.cuda.synchronize()
     assert np.all(np.abs(xt.cpu().numpy() - want) <= 4e-6 * want)
+    assert sm.softmax_exchange_status() == {"join_give_ups": 0, "wait_give_ups": 0,
+                                            "entries_in_use": 0}
+
+
+def test_more_rows_than_a_group():
+    """70 rows of 1048577 columns: a group of launches holds 256 MiB of x, 63
+    rows, so a second one follows, of other workgroup and entry counts."""
+    rows, cols = 70, (1 << 20) + 1
+    print(f"[long] {rows}x{cols}", flush=True)
+    p = sm.softmax_plan(rows, cols)
+    assert p["kernel_name"] == "split_row" and p["launches"] == 4, p
+    x = workloads.random_logits(rows, cols, seed=70, kind="offset")
+    xt = torch.from_numpy(x).to("cuda:0")
+    y, lg = sm.softmax_fwd(xt), sm.softmax_log_fwd(xt)
+    again = sm.softmax_fwd(xt)
+    torch.cuda.synchronize()
+    assert torch.equal(y, again)
+    for a in range(0, rows, 7):
+        want = oracle.softmax_clipped(x[a:a + 7])
+        got = y[a:a + 7].cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got - want) <= 4e-6 * want), a
+        lw = oracle.log_softmax_clipped(x[a:a + 7], -64.0)
+        err = np.abs(lg[a:a + 7].cpu().numpy() - lw)
+        assert np.all(err <= 2e-6 + 2.5e-7 * (np.abs(lw) + math.log(cols))), a
     assert sm.softmax_exchange_status() == {"join_give_ups": 0, "wait_give_ups": 0,
                                             "entries_in_use": 0}
 
