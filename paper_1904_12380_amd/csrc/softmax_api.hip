@@ -669,12 +669,12 @@ Shape default_shape(const float* x, const float* y, int64_t cols, int em) {
 // One workgroup of kRowThreads threads per row, with as many strips per lane
 // as the row needs: false where the library never takes such rows.
 bool row_block_shape(const float* x, const float* y, int64_t cols, int em, Shape* out) {
-  if (!aligned16(x) || !aligned16(y) || cols < kRowMinCols || cols > kRowOverSplitMaxCols + 3 ||
-      (cols > kRowMaxCols && cols <= kSplitMinColsProb))
-    return false;
   const bool ph = cols % 4 != 0;
-  const int64_t strips = ceil_div(cols + (ph ? 3 : 0), int64_t(4) * kRowThreads);
-  if (strips > 24) return false;
+  const int64_t span = cols + (ph ? 3 : 0);  // what the strips must cover
+  if (!aligned16(x) || !aligned16(y) || cols < kRowMinCols || span > kRowOverSplitMaxCols + 3 ||
+      (span > kRowMaxCols && cols <= kSplitMinColsProb))
+    return false;
+  const int64_t strips = ceil_div(span, int64_t(4) * kRowThreads);
   Shape s;
   s.kernel = SOFTMAX_KERNEL_BLOCK_ROW;
   s.vec4 = true;

@@ -90,3 +90,16 @@ def test_a_plan_runs_as_planned(rows, cols):
     plan = sm.softmax_plan(rows, cols, x.data_ptr(), y.data_ptr())
     sm.softmax_fwd_planned(x, plan, out=y)
     assert torch.equal(y, sm.softmax_fwd(x))
+
+
+@pytest.mark.parametrize("cols,threads", [(5117, 256), (10236, 256), (10237, 256), (10238, 1024),
+                                          (10239, 1024), (10240, 256), (10241, 1024)])
+def test_ten_strips_at_most(cols, threads):
+    """256 threads take rows of up to ten strips per lane, the columns that a
+    row's start phase adds among them; the next instance has twenty."""
+    print(f"[row-blocks] {cols}", flush=True)
+    for rows in (1, 5, 3000):
+        p = sm.softmax_plan(rows, cols)
+        assert (p["kernel_name"], p["block_threads"]) == ("block_row", threads), p
+        assert p["elems_per_lane"] * threads < 2 * cols
+    _check(5, cols)
