@@ -207,9 +207,11 @@ constexpr int64_t kBlockOverSplitMaxRowsNum = 15;  // rows <= CUs * 15/16
 constexpr int64_t kBlockOverSplitMaxRowsDen = 16;
 
 // Split rows, two passes (rows too long for the one-pass shapes): the plan
-// names them in 512 x 8 chunks.  Both kernels run about four workgroups per CU
+// names them in 512 x 8 chunks.  Both kernels run up to four workgroups per CU
 // and group of rows (8 x 4194304: 2, 4 and 8 per CU within 3%; 1 x 33554432
-// slower by 20-70% with 8 and 16), at least one step of columns each.  A group
+// slower by 20-70% with 8 and 16; a few more than are resident cost a second
+// round, 64 x 1048577 158 us with 17 a row and 149 with 16), at least one step
+// of columns each.  A group
 // holds up to 256 MiB of x, so that the second kernel finds as much of it as
 // can be in the memory-side cache: 3 x 16777217 ran 112 us in one group and
 // 188 in three, 32 x 4194304 264 us in groups of 256 MiB, 277 of 128 and 300
@@ -776,7 +778,7 @@ bool requested_shape(const softmax_plan_t& want, const float* x, const float* y,
 // columns that each of them takes.
 int long_workgroups(int64_t nb, int64_t cols, const DeviceFacts& f, int64_t* chunk) {
   const int64_t want = std::min({int64_t(kLongMaxEntries) * xch::kEntrySlots,
-                                 ceil_div(kLongWorkgroupsPerCU * f.cus, nb),
+                                 std::max<int64_t>(1, kLongWorkgroupsPerCU * f.cus / nb),
                                  ceil_div(cols, int64_t(4) * kLongStrips * kLongThreads)});
   *chunk = (ceil_div(cols, want) + 3) & ~int64_t(3);
   return static_cast<int>(ceil_div(cols, *chunk));
@@ -1183,8 +1185,10 @@ constexpr int64_t kNllLongCols = 32768;
 constexpr int64_t kNllManyRowsPerCU = 4;
 // Up to half as many rows as CUs: rows of more than kNllSplitCols +
 // kNllSplitColsPerRow * rows columns are split over workgroups of 512
-// threads, so that about four per CU share the launch's bytes in chunks of
-// at least kNllSplitMinChunk columns.  Measured split against the best single
+// threads, so that up to four per CU (all that are resident: a few workgroups
+// more are a second round, 72 x 150008 14.7 us with 15 chunks a row and 13.6
+// with 14) share the launch's bytes in chunks of at least kNllSplitMinChunk
+// columns.  Measured split against the best single
 // workgroup per row: 64 x 262144 14.6 us (unsplit 20 and more), 30 x 50001
 // 6.4 against 7.0, 20 x 30003 5.6 and 5.6, 64 x 32768 6.3 against 5.3,
 // 100 x 50001 8.9 against 8.5, 200 x 131072 20.3 against 18.9.
@@ -1269,7 +1273,7 @@ hipError_t run_nll(const float* x, float* y, const int64_t* labels, int64_t rows
   }
   // At most CUs / 2 rows, each of at least five chunks: one launch.
   const int64_t want = std::min({int64_t(xch::kEntrySlots),
-                                 ceil_div(kNllSplitWorkgroupsPerCU * f.cus, rows),
+                                 kNllSplitWorkgroupsPerCU * f.cus / rows,
                                  ceil_div(cols, kNllSplitMinChunk)});
   int64_t chunk = (ceil_div(cols, want) + 3) & ~int64_t(3);
   int chunks = static_cast<int>(ceil_div(cols, chunk));
