@@ -1176,7 +1176,8 @@ constexpr int64_t kNllGroupMaxStrips = 512;
 // with 64; 209 x 10000 4.65 with 1024 and 4.9 with 512; 128 x 40000 7.3 with 1024 against 7.6 with 512; but 400 x 65539
 // 18.5 with 256 and 20.1 with 512 or 1024.  Long rows that fill the device
 // four times over take 1024 threads: 4096 x 50001 ran 125.5 us, against
-// 129.8 with 512 and 133.7 with 256.
+// 129.8 with 512 and 133.7 with 256.  A row that one step of fewer threads
+// holds takes those: 30 x 5008 4.6 us with 512 threads and 5.0 with 1024.
 constexpr int64_t kNllMidCols = 8192;
 constexpr int64_t kNllMinThreadsPerCU = 384;
 constexpr int64_t kNllMinThreadsPerCUShort = 512;
@@ -1252,7 +1253,7 @@ int nll_threads(int64_t rows, int64_t cols, const DeviceFacts& f) {
   int nt = cols < kNllMidCols ? 64 : 256;
   const int64_t busy =
       f.cus * (cols < kNllShortCols ? kNllMinThreadsPerCUShort : kNllMinThreadsPerCU);
-  while (nt < 1024 && rows * nt < busy && int64_t(8) * nt <= cols)
+  while (nt < 1024 && rows * nt < busy && int64_t(4) * kNllStrips * nt < cols)
     nt = nt == 64 ? 256 : 2 * nt;
   return nt;
 }
