@@ -51,31 +51,51 @@ constexpr int kBlockThreads = 1024;
 // row needs (the wavefront and the 1024-thread kernels round them up to a
 // power of two and keep at most two rows of 1024 threads on a CU): rows of
 // 1088 to 4096 columns, probability rows up to 10240 (logs, which keep their
-// logits too, to 5120), and rows of 16381 to 24576 columns, which the split
+// logits too, to 5120), and rows of 16385 columns and more that the split
 // kernel cuts into three chunks.  16-byte aligned x and y, whole strips or
-// with the row phase.  Measured at 2 to 256 MiB against those kernels:
+// with the row phase.  The lines (small_block_shape) are where it stops being
+// the faster one, on 4 to 32000 rows of each width, calls of 16 KiB to 256 MiB:
 //  * 2049 x 64 MiB 28.1 -> 24.6 us, 3001 x 2 MiB 7.1 -> 3.9, 4096 x 8 MiB
 //    6.1 -> 4.8, 5000 x 64 MiB 28.4 -> 25.2, 1801 x 8 MiB 6.9 -> 5.4,
-//    8192 x 24 MiB 1.35 times faster, 18001 x 256 MiB 116 -> 100;
+//    8192 x 24 MiB 1.35 times faster; below 2 MiB 1.05 to 1.9 times on 1 to
+//    100 rows of 1100 to 5000 columns (64 x 3000 5.1 -> 3.8 us), level on 6144
+//    to 8192, 1.1 times on 9000 to 10240;
 //  * from 1025 to 1087 columns it lost up to 5% at 64 MiB, past 10240 up to
 //    10% from 128 MiB on (14000: 47.4 against 51.7 us) and 17% on few ragged
 //    rows, logs past 5120 up to 22% on few rows (14000 x 2 MiB 4.8 against
 //    6.1);
 //  * with between about one and two rounds of its resident workgroups (8 per
 //    CU) its last round is part empty while the wavefront kernel still runs
-//    one: whole strips of up to 4096 columns lost up to 18% there and keep the
-//    wavefront kernel (2048 columns at 8 to 22 rows per CU, 3072 at 6 to 17,
-//    4096 at 5 to 13; ragged probability rows, 6% at 11 to 13);
-//  * from 16381 columns on, ragged rows gain from a third of a row per CU
-//    (18001 x 116 9.9 -> 8.7 us, x 3728 116 -> 100), whole strips with more
-//    rows than CUs and up to 8 per CU (24000 x 699 29.2 -> 26.0, 17000 x 308
-//    11.8 -> 10.8; 20000 x 3355 2% slower), ragged log rows from two per CU
-//    (18001 x 932 36.0 -> 26.8 us, 20001 x 262 2% slower).
+//    one: rows of up to 4096 columns lose there and keep the wavefront kernel
+//    (rows per CU: whole strips of 2048 columns 8 to 22, 3072 6 to 17, 4096 5
+//    to 13, up to 18%; ragged probability rows 8% at 8 to 13, from 3585 columns
+//    6 to 13 (2300 x 3901 15.3 against 16.1 us); ragged log rows of up to 2048
+//    columns 11% at 8 to 13);
+//  * rows of up to 1280 columns fill a third of its lanes' second strip: past 8
+//    per CU 3 to 12% slower (16000 x 1088 26.4 against 29.2 us; log rows level,
+//    ragged ones faster from 16), and whole strips 3 to 5% at 2 to 4;
+//  * ragged rows whose strips the 1024-thread kernel's two per lane hold (span
+//    6145 to 8192) lose 3 to 11% while every row has a place there, two per CU
+//    (74 x 6803 5.5 against 6.2 us), and gain 10 to 27% on more;
+//  * against the split kernel, ragged rows of up to 20 strips gain from a third
+//    of a row per CU (18001 x 116 9.9 -> 8.7 us, x 3728 116 -> 100); whole
+//    strips while a CU holds all its rows, up to two (17000 x 400 14.0 -> 12.2),
+//    and between 3 and 6 per CU, where the split kernel takes a launch more
+//    than it fills (17000 x 1024 30.6 -> 27.8; but x 600 16.8 against 19.8);
+//    16384 columns, two full chunks, up to 23% slower (800 rows 18.5 against
+//    24.0); 21 to 24 strips lose up to 16% and gain 6% at most (600 x 24570
+//    22.3 against 26.6);
+//  * ragged log rows, whose split kernel has 32-bit access, gain from two per
+//    CU at any such length (18001 x 932 36.0 -> 26.8 us, 24573 x 1024 45.6 ->
+//    40.7).
 constexpr int kRowThreads = 256;
 constexpr int64_t kRowMinCols = 1088;
+constexpr int64_t kRowThinMaxCols = 1280;
 constexpr int64_t kRowMaxCols = 10240;
 constexpr int64_t kRowMaxColsLog = 5120;
-constexpr int64_t kRowOverSplitMaxCols = 24576 - 3;  // with a phase: 24 strips
+constexpr int64_t kRowOverSplitMinCols = 16384;
+constexpr int64_t kRowOverSplitSpan = 20480;    // probability rows: 20 strips
+constexpr int64_t kRowOverSplitMaxSpan = 24576;  // log rows and a caller's plan: 24
 // Probability and log rows longer than this take the one-pass split kernel
 // rather than one workgroup per row (measured with the dispatch sweep,
 // paper_1904_12380_amd/sweep.py).  Per 64 MiB of logits, 16384 columns ran
@@ -201,7 +221,7 @@ constexpr int64_t kSplitWidePadDen = 16;  // extra padding of at least cols / 16
 // 255 rows 1.3% slower.  At the bounds: 46-81 rows ran 3-6% faster split,
 // 89-105 rows 5-7% faster in one workgroup; 243 and 256 rows of 20480
 // columns 1.5-2.5% faster split.  With more rows than CUs:
-// kRowOverSplitMaxCols.
+// small_block_shape.
 constexpr int64_t kBlockOverSplitMinRowsDen = 3;   // rows >= CUs / 3
 constexpr int64_t kBlockOverSplitMaxRowsNum = 15;  // rows <= CUs * 15/16
 constexpr int64_t kBlockOverSplitMaxRowsDen = 16;
@@ -673,7 +693,7 @@ Shape default_shape(const float* x, const float* y, int64_t cols, int em) {
 bool row_block_shape(const float* x, const float* y, int64_t cols, int em, Shape* out) {
   const bool ph = cols % 4 != 0;
   const int64_t span = cols + (ph ? 3 : 0);  // what the strips must cover
-  if (!aligned16(x) || !aligned16(y) || cols < kRowMinCols || span > kRowOverSplitMaxCols + 3 ||
+  if (!aligned16(x) || !aligned16(y) || cols < kRowMinCols || span > kRowOverSplitMaxSpan ||
       (span > kRowMaxCols && cols <= kSplitMinColsProb))
     return false;
   const int64_t strips = ceil_div(span, int64_t(4) * kRowThreads);
@@ -840,26 +860,36 @@ int group_rows_steps(int64_t rows, int em, int dev, const DeviceFacts& f, Shape*
 }
 
 // One workgroup of kRowThreads threads per row where that is the fastest
-// (kRowMinCols and below it): fills in the shape and returns true.
+// (kRowMinCols and above it): fills in the shape and returns true.
 bool small_block_shape(const float* x, const float* y, int64_t rows, int64_t cols, int em,
                        const DeviceFacts& f, Shape* out) {
   const bool ph = cols % 4 != 0;
   const bool log = em == kLogOut;
+  const int64_t span = cols + (ph ? 3 : 0);
+  // More than `lo` and at most `hi` rows per CU.
   auto between = [&](int64_t lo, int64_t hi) { return rows > lo * f.cus && rows <= hi * f.cus; };
+  auto above = [&](int64_t lo) { return rows > lo * f.cus; };
   bool take = false;
   if (cols < kRowMinCols) {
     take = false;
+  } else if (cols <= kRowThinMaxCols) {
+    take = ph && log ? !between(8, 16) : ph ? !above(8) : !above(8) && !between(2, 4);
   } else if (cols <= kWaveRowMaxCols) {
-    take = ph                             ? log || !between(11, 13)
-           : cols <= kWaveRowMaxColsScalar ? !between(8, 22)
-           : cols <= 3072                  ? !between(6, 17)
+    if (ph && log)
+      take = cols > kWaveRowMaxColsScalar || !between(8, 13);
+    else if (ph)
+      take = cols <= 3072 ? !between(11, 13) : cols <= 3584 ? !between(8, 13) : !between(6, 13);
+    else
+      take = cols <= kWaveRowMaxColsScalar ? !between(8, 22)
+             : cols <= 3072                ? !between(6, 17)
                                            : !between(5, 13);
   } else if (cols <= kRowMaxCols) {
-    take = !log || cols <= kRowMaxColsLog;
-  } else if (cols > kSplitMinColsProb && cols <= kRowOverSplitMaxCols) {
-    take = log  ? ph && rows >= 2 * f.cus
-           : ph ? 3 * rows >= f.cus
-                : rows > f.cus && rows <= 8 * f.cus;
+    take = log ? cols <= kRowMaxColsLog : !ph || span <= 6144 || span > 8192 || above(2);
+  } else if (cols > kRowOverSplitMinCols) {
+    take = log ? ph && rows >= 2 * f.cus
+           : span > kRowOverSplitSpan ? false
+           : ph                       ? 3 * rows >= f.cus
+                                      : between(1, 2) || between(3, 6);
   }
   if (!take) return false;
   return row_block_shape(x, y, cols, em, out);
@@ -1177,7 +1207,7 @@ constexpr int64_t kNllGroupMaxStrips = 512;
 // 18.5 with 256 and 20.1 with 512 or 1024.  Long rows that fill the device
 // four times over take 1024 threads: 4096 x 50001 ran 125.5 us, against
 // 129.8 with 512 and 133.7 with 256.  A row that one step of fewer threads
-// holds takes those: 30 x 5008 4.6 us with 512 threads and 5.0 with 1024.
+// holds takes those: 30 x 5008 4.4 us with 512 threads and 4.6 with 1024.
 constexpr int64_t kNllMidCols = 8192;
 constexpr int64_t kNllMinThreadsPerCU = 384;
 constexpr int64_t kNllMinThreadsPerCUShort = 512;
@@ -1187,7 +1217,7 @@ constexpr int64_t kNllManyRowsPerCU = 4;
 // Up to half as many rows as CUs: rows of more than kNllSplitCols +
 // kNllSplitColsPerRow * rows columns are split over workgroups of 512
 // threads, so that up to four per CU (all that are resident: a few workgroups
-// more are a second round, 72 x 150008 14.7 us with 15 chunks a row and 13.6
+// more are a second round, 72 x 150008 14.8 us with 15 chunks a row and 13.7
 // with 14) share the launch's bytes in chunks of at least kNllSplitMinChunk
 // columns.  Measured split against the best single
 // workgroup per row: 64 x 262144 14.6 us (unsplit 20 and more), 30 x 50001

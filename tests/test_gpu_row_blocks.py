@@ -103,3 +103,50 @@ def test_ten_strips_at_most(cols, threads):
         assert (p["kernel_name"], p["block_threads"]) == ("block_row", threads), p
         assert p["elems_per_lane"] * threads < 2 * cols
     _check(5, cols)
+
+
+# columns, rows per CU (num / den, +1 row), kernel, threads: both sides of the
+# lines between the 256-thread kernel and the others.
+LINES = [(1100, 2, 1, 0, "block_row", 256), (1100, 2, 1, 1, "wave_row", 256),
+         (1280, 8, 1, 0, "block_row", 256), (1280, 8, 1, 1, "wave_row", 256),
+         (1201, 8, 1, 0, "block_row", 256), (1201, 8, 1, 1, "wave_row", 256),
+         (1284, 2, 1, 1, "block_row", 256), (1284, 8, 1, 1, "wave_row", 256),
+         (3073, 8, 1, 0, "block_row", 256), (3073, 8, 1, 1, "wave_row", 256),
+         (3585, 6, 1, 1, "wave_row", 256), (3585, 13, 1, 1, "block_row", 256),
+         (6141, 1, 1, 0, "block_row", 256), (6142, 2, 1, 0, "block_row", 1024),
+         (6142, 2, 1, 1, "block_row", 256), (8189, 2, 1, 0, "block_row", 1024),
+         (8190, 2, 1, 0, "block_row", 256), (6144, 1, 1, 0, "block_row", 256),
+         (16384, 3, 2, 0, "split_row", 256), (16388, 3, 2, 0, "block_row", 256),
+         (20480, 5, 2, 0, "split_row", 256), (20480, 4, 1, 0, "block_row", 256),
+         (20480, 6, 1, 1, "split_row", 256), (20484, 3, 2, 0, "split_row", 256),
+         (20477, 1, 2, 0, "block_row", 256), (20478, 1, 2, 0, "split_row", 256),
+         (24573, 3, 1, 0, "split_row", 256)]
+
+
+@pytest.mark.parametrize("cols,num,den,more,kernel,threads", LINES)
+def test_lines(cols, num, den, more, kernel, threads):
+    rows = _cus() * num // den + more
+    p = sm.softmax_plan(rows, cols)
+    print(f"[row-blocks] {rows}x{cols} {p['kernel_name']} {p['block_threads']}", flush=True)
+    assert (p["kernel_name"], p["block_threads"]) == (kernel, threads), p
+
+
+@pytest.mark.parametrize("cols", [2047, 16388, 20477, 20478, 24573])
+def test_rows_over_the_split_kernel(cols):
+    """Row counts past two and three per CU, where log rows and probability rows
+    go different ways."""
+    for rows in (2 * _cus(), 3 * _cus() + 1):
+        print(f"[row-blocks] {rows}x{cols}", flush=True)
+        _check(rows, cols)
+
+
+def test_a_plan_of_24_strips_still_runs():
+    """A caller's plan may ask for 256 threads on rows of 21 to 24 strips, which
+    the library itself gives to the split kernel."""
+    for cols in (20484, 24000, 24570):
+        print(f"[row-blocks] planned {cols}", flush=True)
+        x = torch.randn(40, cols, device="cuda:0")
+        y = sm.softmax_fwd_planned(x, dict(kernel_name="block_row", vec_width=4,
+                                           block_threads=256))
+        want = oracle.softmax_clipped(x.cpu().numpy())
+        assert np.all(np.abs(y.cpu().numpy() - want) <= 4e-6 * want)
