@@ -157,6 +157,16 @@ constexpr int64_t kGroupRowsOneStepDen = 10;
 constexpr int64_t kPackedWideCols = 192;
 constexpr int64_t kPackedMinRowsPerCU = 4;
 constexpr int64_t kPackedMinRowsPerCUWide = 32;
+// Log rows, whose wavefronts lose less against the tiles: the tiles gain from
+// 12 rows per CU with up to 10 columns per lane (4000 x 65 4.1 against 3.9 us,
+// 1400 x 130 3.9 and 3.9) and from 32 with more (2000 x 127 3.9 against 4.7,
+// 12000 x 127 6.2 and 5.7); in x or y that are not 16-byte aligned from 32
+// (2000 x 79 3.5 against 4.5, 12000 x 79 6.0 and 5.2) and 40 (1952 x 114 3.9
+// against 5.3, 16000 x 127 7.4 and 6.7).
+constexpr int kLogPackedThinEpl = 10;
+constexpr int64_t kLogPackedMinRowsPerCUThin = 12;
+constexpr int64_t kLogPackedMinRowsPerCU = 32;
+constexpr int64_t kLogPackedMinRowsPerCUUnaligned = 40;
 // Log rows past this fill a wavefront's four 32-bit loads: 67108 x 250 ran
 // 25.1 us so and 26.1 packed (65793 x 255 26.8 and 26.3, 129055 x 130 35.2
 // and 24.6).
@@ -916,6 +926,15 @@ Shape scalar_row_shape(int64_t cols) {
   return s;
 }
 
+// Rows per CU up to which rows of more than kPackedMaxCols columns in packed
+// shape s take one wavefront per row instead (kPackedMinRowsPerCU).
+int64_t packed_min_rows_per_cu(const Shape& s, int64_t cols, int em) {
+  if (em != kLogOut) return cols > kPackedWideCols ? kPackedMinRowsPerCUWide : kPackedMinRowsPerCU;
+  if (s.epl <= kLogPackedThinEpl)
+    return s.vec4 ? kLogPackedMinRowsPerCUThin : kLogPackedMinRowsPerCU;
+  return s.vec4 ? kLogPackedMinRowsPerCU : kLogPackedMinRowsPerCUUnaligned;
+}
+
 // The library's shape once rows and the device are known: rows of at most
 // 256 columns in whole strips take the grouped-rows kernel or the packed
 // kernel by the rules measured above (kGroupRowsMinFill, kGroupRowsOneStep
@@ -929,7 +948,7 @@ int library_shape(const float* x, const float* y, int64_t rows, int64_t cols, in
     return SOFTMAX_OK;
   }
   if ((s.kernel == SOFTMAX_KERNEL_PACKED && s.g >= 8 &&
-       (rows <= f.cus * (cols > kPackedWideCols ? kPackedMinRowsPerCUWide : kPackedMinRowsPerCU) ||
+       (rows <= f.cus * packed_min_rows_per_cu(s, cols, em) ||
         (em == kLogOut && cols > kLogPackedMaxCols))) ||
       (em == kLogOut && s.ph &&
        (s.kernel == SOFTMAX_KERNEL_SPLIT_ROW || rows < kLogPhaseMinRowsPerCU * f.cus))) {

@@ -79,3 +79,13 @@ def test_phase_rows(cols):
 def test_split(rows, cols):
     print(f"[log-rows] split {rows}x{cols}", flush=True)
     _check(rows, cols, NEG_INF, 4)
+
+
+# Rows per CU where log rows change from a wavefront each to packed tiles: by
+# columns per lane (65 and 130: 9; 98 and 127: 13 and 16) and alignment.
+@pytest.mark.parametrize("cols,per_cu,off", [(65, 12, 4), (130, 12, 4), (127, 32, 4), (224, 32, 4),
+                                             (79, 32, 1), (98, 40, 3), (190, 40, 1)])
+def test_packed_lines(cols, per_cu, off):
+    for rows in (per_cu * _cus(), per_cu * _cus() + 1):
+        print(f"[log-rows] {rows}x{cols}+{off}", flush=True)
+        _check(rows, cols, NEG_INF, off)
