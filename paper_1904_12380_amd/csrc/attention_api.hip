@@ -58,26 +58,52 @@ hipError_t run_attention_dam(const float* q, const float* k, const float* v, flo
 // the DAM tile.
 
 // Instances: NQ x NK x access (rows of whole 128-byte lines read once: nt
-// loads; other rows of whole 16-byte strips; other rows).
-enum WaveAccess { kWaveStream, kWaveWhole, kWaveRagged };
+// loads; other rows of whole 16-byte strips; other rows; and the last two with
+// plain stores, for up to kAttnPlainMaxKeyTiles key tiles).
+enum WaveAccess { kWaveStream, kWaveWhole, kWaveRagged, kWaveWholePlain, kWaveRaggedPlain };
+constexpr int kWaveAccesses = 5;
 
-template <int NQ, bool RAGGED, bool STREAM>
-const void* wave_fn_nk(int nk) {
+// Outputs of at least this many bytes, in rows that are not whole 32-byte
+// sectors, are stored without the nontemporal policy where few enough keys
+// leave the stores the larger part of the work (up to kAttnPlainMaxKeyTiles
+// key tiles, from kAttnPlainMinDv columns): a row's neighbouring blocks then
+// meet in the L2 instead of leaving it as partial sectors.  64 x 512 x 16 x 8 x
+// 604 40.2 -> 26.6 us, 147 x 1401 x 13 x 8 x 94 45.3 -> 29.1, 421 x 76 x 40 x 408
+// x 769 100.8 -> 92.4; but with 64 keys 64 x 512 x 64 x 8 x 604 45.0 -> 49.1, on
+// 38 MiB 64 x 256 x 48 x 8 x 604 21.8 -> 23.7, on 58 columns 42.9 -> 48.1.
+constexpr int64_t kAttnPlainMinBytes = int64_t(64) << 20;
+constexpr int kAttnPlainMaxKeyTiles = 3;
+constexpr int kAttnPlainMinDv = 64;
+
+template <int NQ, int NK>
+const void* wave_fn_access(WaveAccess access) {
   auto cast = [](auto f) { return reinterpret_cast<const void*>(f); };
-  switch (nk) {
-    case 1: return cast(&k_attention_wave<NQ, 1, RAGGED, STREAM>);
-    case 2: return cast(&k_attention_wave<NQ, 2, RAGGED, STREAM>);
-    case 3: return cast(&k_attention_wave<NQ, 3, RAGGED, STREAM>);
-    default: return cast(&k_attention_wave<NQ, 4, RAGGED, STREAM>);
+  if constexpr (NK <= kAttnPlainMaxKeyTiles) {
+    if (access == kWaveWholePlain) return cast(&k_attention_wave<NQ, NK, false, false, true>);
+    if (access == kWaveRaggedPlain) return cast(&k_attention_wave<NQ, NK, true, false, true>);
+  }
+  switch (access) {
+    case kWaveStream: return cast(&k_attention_wave<NQ, NK, false, true, false>);
+    case kWaveWhole: return cast(&k_attention_wave<NQ, NK, false, false, false>);
+    default: return cast(&k_attention_wave<NQ, NK, true, false, false>);
   }
 }
 
-template <bool RAGGED, bool STREAM>
-const void* wave_fn(int nq, int nk) {
+template <int NQ>
+const void* wave_fn_nk(int nk, WaveAccess access) {
+  switch (nk) {
+    case 1: return wave_fn_access<NQ, 1>(access);
+    case 2: return wave_fn_access<NQ, 2>(access);
+    case 3: return wave_fn_access<NQ, 3>(access);
+    default: return wave_fn_access<NQ, 4>(access);
+  }
+}
+
+const void* wave_fn(int nq, int nk, WaveAccess access) {
   switch (nq) {
-    case 1: return wave_fn_nk<1, RAGGED, STREAM>(nk);
-    case 2: return wave_fn_nk<2, RAGGED, STREAM>(nk);
-    default: return wave_fn_nk<3, RAGGED, STREAM>(nk);
+    case 1: return wave_fn_nk<1>(nk, access);
+    case 2: return wave_fn_nk<2>(nk, access);
+    default: return wave_fn_nk<3>(nk, access);
   }
 }
 
@@ -92,7 +118,7 @@ constexpr int64_t kAttnMinWavesPerCU = 4;
 
 // Resident workgroups per CU of an instance, from the runtime's occupancy
 // calculator (the same on every gfx950 device), once per instance.
-std::atomic<int> g_wave_per_cu[3][4][3][2];
+std::atomic<int> g_wave_per_cu[3][4][kWaveAccesses][2];
 
 int wave_per_cu(const void* fn, int nq, int nk, WaveAccess access, int waves, int* out) {
   std::atomic<int>& slot = g_wave_per_cu[nq - 1][nk - 1][access][waves > 1];
@@ -116,12 +142,13 @@ int run_attention_wave(const float* q, const float* k, const float* v, float* o,
   while (nq > 1 && blocks(nq) < kAttnMinWavesPerCU * cus) --nq;
   const int nk = (lk + 15) / 16;
   const int64_t items = blocks(nq);
-  const WaveAccess access = d % 4 != 0 ? kWaveRagged
+  const bool plain = dv % 8 != 0 && dv >= kAttnPlainMinDv && nk <= kAttnPlainMaxKeyTiles &&
+                     batch * lq * dv * 4 >= kAttnPlainMinBytes;
+  const WaveAccess access = d % 4 != 0 ? (plain ? kWaveRaggedPlain : kWaveRagged)
+                            : plain    ? kWaveWholePlain
                             : items == batch && d % 32 == 0 && dv % 32 == 0 ? kWaveStream
                                                                             : kWaveWhole;
-  const void* fn = access == kWaveRagged   ? wave_fn<true, false>(nq, nk)
-                   : access == kWaveStream ? wave_fn<false, true>(nq, nk)
-                                           : wave_fn<false, false>(nq, nk);
+  const void* fn = wave_fn(nq, nk, access);
   // Four wavefronts per workgroup share a batch element's K and V through
   // their CU's cache; at most one item per CU takes a CU each (100 x 16 x 50 x
   // 200 x 200 ran 13.4 us so, 17.8 on 25 CUs).

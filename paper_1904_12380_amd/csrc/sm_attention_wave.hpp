@@ -38,8 +38,11 @@
 namespace smx {
 
 // Cache policy of the operand loads and of the output stores (the aux
-// argument of the buffer instructions): nontemporal.  Stores always take it
-// (3-7% on most shapes).  Loads take it (STREAM) where one wavefront reads
+// argument of the buffer instructions): nontemporal.  Stores take it (3-7% on
+// most shapes, up to 40% on large outputs of whole 32-byte rows) but on large
+// outputs whose rows are not whole 32-byte sectors (PLAIN; the rule is beside
+// kAttnPlainMinBytes).  The policy is an instruction field: chosen by a branch
+// at run time, the stores cost 2% on average and up to 12%.  Loads take it (STREAM) where one wavefront reads
 // all of a batch element's K and V and rows are whole 128-byte lines: 64 x 64
 // heads of d = 64 115 -> 108 us per 8192, 40 x 60 of d = 256 80 -> 75 per
 // 2048; elsewhere the next loads or wavefronts want the same lines, and it
@@ -83,20 +86,21 @@ __device__ __forceinline__ void buf_load_n(float (&v)[4], __amdgpu_buffer_rsrc_t
   }
 }
 
-template <int N>
+template <int N, bool PLAIN>
 __device__ __forceinline__ void buf_store_n(__amdgpu_buffer_rsrc_t r, unsigned off,
                                             const float (&v)[4]) {
+  constexpr int kAux = PLAIN ? 0 : kAttnNt;
   const int o = static_cast<int>(off);
   if constexpr (N == 4)
     __builtin_amdgcn_raw_buffer_store_b128(
-        u32x4m{as_u32(v[0]), as_u32(v[1]), as_u32(v[2]), as_u32(v[3])}, r, o, 0, kAttnNt);
+        u32x4m{as_u32(v[0]), as_u32(v[1]), as_u32(v[2]), as_u32(v[3])}, r, o, 0, kAux);
   else if constexpr (N == 3)
     __builtin_amdgcn_raw_buffer_store_b96(u32x3m{as_u32(v[0]), as_u32(v[1]), as_u32(v[2])}, r, o,
-                                          0, kAttnNt);
+                                          0, kAux);
   else if constexpr (N == 2)
-    __builtin_amdgcn_raw_buffer_store_b64(u32x2m{as_u32(v[0]), as_u32(v[1])}, r, o, 0, kAttnNt);
+    __builtin_amdgcn_raw_buffer_store_b64(u32x2m{as_u32(v[0]), as_u32(v[1])}, r, o, 0, kAux);
   else
-    __builtin_amdgcn_raw_buffer_store_b32(as_u32(v[0]), r, o, 0, kAttnNt);
+    __builtin_amdgcn_raw_buffer_store_b32(as_u32(v[0]), r, o, 0, kAux);
 }
 
 template <bool STREAM>
@@ -148,7 +152,7 @@ __device__ __forceinline__ void attn_v_load(AttnV& a, __amdgpu_buffer_rsrc_t rv,
 // 0 .. VD - 1 are in vr (or on their way), tile kt at slot kt % VD; a slot is
 // loaded again as soon as it has been used, with this block's tile kt + VD or
 // (U = 4) the next block's first ones, at next_col.
-template <int NQ, int NK, int VD, int U, bool STREAM>
+template <int NQ, int NK, int VD, int U, bool STREAM, bool PLAIN>
 __device__ __forceinline__ void attn_pv_block(const float (&p)[NQ][4 * NK], AttnV (&vr)[VD],
                                               __amdgpu_buffer_rsrc_t rv,
                                               __amdgpu_buffer_rsrc_t ro, unsigned col,
@@ -188,13 +192,13 @@ __device__ __forceinline__ void attn_pv_block(const float (&p)[NQ][4 * NK], Attn
       float v[4];
 #pragma unroll
       for (int u = 0; u < U; ++u) v[u] = acc[q][u][r];
-      buf_store_n<U>(ro, off + 4u * static_cast<unsigned>((16 * q + r) * dv), v);
+      buf_store_n<U, PLAIN>(ro, off + 4u * static_cast<unsigned>((16 * q + r) * dv), v);
     }
   }
 }
 
 // The last block of a row of value columns, of U < 4 tiles.
-template <int NQ, int NK, int VD, int U, bool STREAM>
+template <int NQ, int NK, int VD, int U, bool STREAM, bool PLAIN>
 __device__ __forceinline__ void attn_pv_last(const float (&p)[NQ][4 * NK], AttnV (&vr)[VD],
                                              bool loaded, __amdgpu_buffer_rsrc_t rv,
                                              __amdgpu_buffer_rsrc_t ro, int c0, int dv, int lk,
@@ -204,7 +208,7 @@ __device__ __forceinline__ void attn_pv_last(const float (&p)[NQ][4 * NK], AttnV
 #pragma unroll
     for (int kt = 0; kt < VD; ++kt) attn_v_load<U, STREAM>(vr[kt], rv, col, dv, kt, g);
   }
-  attn_pv_block<NQ, NK, VD, U, STREAM>(p, vr, rv, ro, col, 0u, dv, lk, g);
+  attn_pv_block<NQ, NK, VD, U, STREAM, PLAIN>(p, vr, rv, ro, col, 0u, dv, lk, g);
 }
 
 // Key tiles of V on their way at once (a divisor of NK: a block's tile 0 is
@@ -212,7 +216,7 @@ __device__ __forceinline__ void attn_pv_last(const float (&p)[NQ][4 * NK], AttnV
 template <int NQ, int NK>
 constexpr int kAttnVDepth = NQ * NK >= 9 ? 1 : NK == 4 ? 2 : NK;
 
-template <int NQ, int NK, bool RAGGED, bool STREAM>
+template <int NQ, int NK, bool RAGGED, bool STREAM, bool PLAIN = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_attention_wave(
     const float* q, const float* k, const float* v, float* o, int64_t batch, int lq, int lk,
     int d, int dv, float scale, Clip clip) {
@@ -394,15 +398,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     for (int cb = 0; cb < n4; ++cb) {
       const unsigned next = cb + 1 < n4 ? attn_col_off<4>(64 * (cb + 1), dv, j)
                                         : static_cast<unsigned>(kBufOff);
-      attn_pv_block<NQ, NK, VD, 4, STREAM>(p, vr, rv, ro, attn_col_off<4>(64 * cb, dv, j), next, dv, lk,
-                                   g);
+      attn_pv_block<NQ, NK, VD, 4, STREAM, PLAIN>(p, vr, rv, ro, attn_col_off<4>(64 * cb, dv, j),
+                                                  next, dv, lk, g);
     }
     if (ulast == 3)
-      attn_pv_last<NQ, NK, VD, 3, STREAM>(p, vr, nfull == 0, rv, ro, 64 * nfull, dv, lk, j, g);
+      attn_pv_last<NQ, NK, VD, 3, STREAM, PLAIN>(p, vr, nfull == 0, rv, ro, 64 * nfull, dv, lk, j,
+                                                 g);
     else if (ulast == 2)
-      attn_pv_last<NQ, NK, VD, 2, STREAM>(p, vr, nfull == 0, rv, ro, 64 * nfull, dv, lk, j, g);
+      attn_pv_last<NQ, NK, VD, 2, STREAM, PLAIN>(p, vr, nfull == 0, rv, ro, 64 * nfull, dv, lk, j,
+                                                 g);
     else if (ulast == 1)
-      attn_pv_last<NQ, NK, VD, 1, STREAM>(p, vr, nfull == 0, rv, ro, 64 * nfull, dv, lk, j, g);
+      attn_pv_last<NQ, NK, VD, 1, STREAM, PLAIN>(p, vr, nfull == 0, rv, ro, 64 * nfull, dv, lk, j,
+                                                 g);
   }
 }
 

@@ -80,3 +80,34 @@ def test_nan_and_inf_stay_in_their_rows():
     assert np.array_equal(np.isnan(got), np.isnan(want))
     fin = ~np.isnan(want)
     assert np.all(np.abs(got[fin] - want[fin]) <= 1e-4)
+
+
+# Outputs of 64 MiB and more in rows that are not whole 32-byte sectors: one,
+# two and three query tiles against one to three key tiles, d and dv whole
+# 16-byte strips and not, the last column block of every width.
+@pytest.mark.parametrize("lq,lk,d,dv", [(10, 5, 8, 100), (20, 16, 9, 94), (40, 15, 8, 188),
+                                        (16, 20, 9, 67), (32, 32, 12, 604), (33, 17, 5, 89),
+                                        (7, 48, 16, 76), (100, 37, 7, 113), (48, 33, 8, 132)])
+def test_large_outputs_of_partial_sectors(lq, lk, d, dv):
+    """The whole output bit for bit against the same batch elements in calls of
+    smaller outputs, and its ends against the oracle."""
+    b = -(-(1 << 24) // (lq * dv)) + 1
+    print(f"[attn-wave] large {b}x{lq}x{lk}x{d}x{dv}", flush=True)
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(lq + dv)
+    q, k, v = (torch.randn(b, n, w, device="cuda:0", generator=g)
+               for n, w in ((lq, d), (lk, d), (lk, dv)))
+    n = b * lq * dv
+    buf = torch.full((n + 8,), CANARY, device="cuda:0")
+    out = buf[4:4 + n].view(b, lq, dv)
+    sm.softmax_attention_fwd(q, k, v, scale=0.3, out=out)
+    step = -(-b // 3)
+    for a in range(0, b, step):
+        part = sm.softmax_attention_fwd(q[a:a + step], k[a:a + step], v[a:a + step], scale=0.3)
+        assert torch.equal(out[a:a + step], part), a
+    edge = torch.cat([buf[:4], buf[4 + n:]]).cpu().numpy()
+    assert np.all(edge == np.float32(CANARY)), "written outside the output"
+    for a in (0, b - 3):
+        qa, ka, va = (t[a:a + 3].cpu().numpy() for t in (q, k, v))
+        want, tol = bound(qa, ka, va, float(np.float32(0.3)), -64.0)
+        assert np.all(np.abs(out[a:a + 3].cpu().numpy().astype(np.float64) - want) <= tol)
