@@ -98,16 +98,12 @@ __device__ __forceinline__ void wait_until_after(uint64_t t, float v) {
 }
 
 // A launch's exchange context: the scratch table, the call's key, the wait
-// limit in wall-clock ticks, and whether the launch's workgroups may claim
-// a free entry (join) or only find the one their row already holds (the
-// second pass of the two-pass kernels).
+// limit in wall-clock ticks and the place of its entries.
 struct XchArgs {
   uint64_t* scratch;
   uint64_t key;
   uint32_t limit_ticks;
-  uint32_t join;
   uint32_t base;  // entry of the launch's row 0 (mod kEntries)
-  uint32_t unused;
 };
 
 // Where the entry of row `lrow` of the launch lies.
@@ -123,23 +119,17 @@ __device__ __forceinline__ uint64_t row_tag(const XchArgs& a, int lrow) {
   return tag == 0 ? 1 : tag;
 }
 
-// Entry of row `lrow` of the launch, joined (or, with a.join == 0, found)
-// by the calling lane; null once `deadline` has passed.
+// Entry of row `lrow` of the launch, joined by the calling lane (claimed if it
+// is free); null once `deadline` has passed.  (The second of the two-pass
+// kernels only looks its entries up: find_entry and row_tag.)
 __device__ __forceinline__ uint64_t* row_entry(const XchArgs& a, int lrow, uint64_t deadline) {
   const uint64_t tag = row_tag(a, lrow);
   uint64_t* entry = find_entry(a, lrow);
   while (true) {
-    uint64_t seen;
-    if (a.join) {
-      uint64_t expected = 0;
-      __hip_atomic_compare_exchange_strong(&entry[0], &expected, tag, __ATOMIC_RELAXED,
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      seen = expected;  // 0 if this call claimed it, else the owner it found
-      if (seen == 0 || seen == tag) return entry;
-    } else {
-      seen = xch::ld_agent(&entry[0]);
-      if (seen == tag) return entry;
-    }
+    uint64_t seen = 0;  // stays 0 if this call claims the entry, else its owner
+    __hip_atomic_compare_exchange_strong(&entry[0], &seen, tag, __ATOMIC_RELAXED,
+                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (seen == 0 || seen == tag) return entry;
     if (static_cast<int64_t>(wall_clock() - deadline) > 0) return nullptr;
     __builtin_amdgcn_s_sleep(2);
   }

@@ -735,14 +735,15 @@ constexpr int kRowWaves = (V <= 8 && VEC4 && !keeps_logits<MODE>()) ? 4 : 2;
 // over before its writes begin (HBM then serves them in two phases rather
 // than interleaved).
 //
-// PH (128-bit access): rows of a length that is not a
-// multiple of 4 in 16-byte aligned x and y, each row accessed in the aligned
-// strips around it (load_strip_ph); the row's phase is (row * cols) mod 4.
+// PH (128-bit access, here for probability outputs): rows of a length that is
+// not a multiple of 4 in 16-byte aligned x and y, each row accessed in the
+// aligned strips around it (load_strip_ph); the row's phase is (row * cols) mod
+// 4.
 template <int V, bool VEC4, int MODE, bool PH = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
     kRowWaves<V, VEC4, MODE>))) void k_wave_row(
     const float* x, float* y, int64_t rows, int64_t cols, Clip clip, uint32_t delay) {
-  static_assert(!PH || VEC4, "phase access is 128-bit access");
+  static_assert(!PH || (VEC4 && !keeps_logits<MODE>()), "phase access: probability outputs");
   const uint64_t t0 = wall_clock();
   const int lane = __lane_id();
   const int wave = threadIdx.x >> 6;
@@ -770,7 +771,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
 
 // ---------------------------------------------------------------------------
 // (c) One workgroup of NT threads per row, cols <= 4*V*NT.  `delay` and PH
-// as for k_wave_row.
+// as for k_wave_row (PH for log outputs too).
 template <int NT, int V, bool VEC4, int MODE, bool PH = false>
 __global__ __launch_bounds__(NT) void k_block_row(const float* x, float* y, int64_t rows,
                                                   int64_t cols, Clip clip, uint32_t delay) {

@@ -90,14 +90,14 @@ __device__ __forceinline__ void release_long_entry(const XchArgs& xa, int e, int
 
 template <int NT, int MODE>
 __global__ __launch_bounds__(NT) void k_long_apply(const float* x, float* y, XchArgs xa,
-                                                   int64_t cols, int wpr, int entries, int apr,
+                                                   int64_t cols, int wpr, int entries,
                                                    int64_t chunk, Clip clip) {
   constexpr int U = kLongStrips;
   __shared__ float bcast[2];
   const int tid = threadIdx.x;
   const int lane = __lane_id();
-  const int lrow = blockIdx.x / apr;
-  const int w = blockIdx.x - lrow * apr;
+  const int lrow = blockIdx.x / wpr;
+  const int w = blockIdx.x - lrow * wpr;
   // Wavefront 0: the row's entries checked, one lane each (k_long_stats has
   // ended, so each holds the row or never will), and its slots merged.
   bool found = false;
@@ -188,14 +188,13 @@ __global__ __launch_bounds__(NT) void k_long_apply(const float* x, float* y, Xch
     // entry by entry out of the first one (counts on one address take about
     // 70 ns each, one after another).
     const int mine = w % entries;
-    const int group = apr / entries + (mine < apr % entries ? 1 : 0);
-    const int groups = apr < entries ? apr : entries;
+    const int group = wpr / entries + (mine < wpr % entries ? 1 : 0);
     uint32_t last = 0;
     if (tid == 0) {
       uint64_t* const e = find_entry(xa, lrow * entries + mine);
       if (depart_entry(e, group, 1u)) {
         uint32_t* const total = reinterpret_cast<uint32_t*>(find_entry(xa, lrow * entries) + 2);
-        last = xch::add_agent32(total, 1u) == static_cast<uint32_t>(groups) - 1u ? 1u : 0u;
+        last = xch::add_agent32(total, 1u) == static_cast<uint32_t>(entries) - 1u ? 1u : 0u;
         if (last) __hip_atomic_store(total, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }

@@ -6,7 +6,8 @@
 // through registers and no value outlives its exponential: there is no limit
 // on the row length, and the loads run a step ahead of the arithmetic.
 //
-//   k_nll_group   rows of at most kNllGroupMaxCols columns: G lanes per row.
+//   k_nll_group   rows of at most 512 aligned strips (kNllGroupMaxStrips, about
+//                 2048 columns): G lanes per row.
 //   k_nll_rows    one wavefront (NT = 64) or one workgroup per row.
 //   k_nll_split   a few long rows: each cut into equal chunks, one workgroup
 //                 per chunk, the last of a row's workgroups to finish merges.

@@ -477,15 +477,10 @@ const void* shape_fn(const Shape& s, bool stats_pass) {
       return packed_shape_fn<EM, VEC4>(s);
     case SOFTMAX_KERNEL_WAVE_ROW:
       if (s.ph) {
-        if constexpr (VEC4) {
-          switch (s.v) {
-            case 1: return cast(&k_wave_row<1, true, EM, true>);
-            case 2: return cast(&k_wave_row<2, true, EM, true>);
-            case 4: return cast(&k_wave_row<4, true, EM, true>);
-            case 8: return cast(&k_wave_row<8, true, EM, true>);
-            case 16: return cast(&k_wave_row<16, true, EM, true>);
-            default: return nullptr;
-          }
+        // Spans of 2052 to 4096 columns; ragged log rows of that length always
+        // take 256 threads.
+        if constexpr (VEC4 && EM != kLogOut) {
+          if (s.v == 16) return cast(&k_wave_row<16, true, EM, true>);
         }
         return nullptr;
       }
@@ -939,7 +934,7 @@ int64_t packed_min_rows_per_cu(const Shape& s, int64_t cols, int em) {
 // 256 columns in whole strips take the grouped-rows kernel or the packed
 // kernel by the rules measured above (kGroupRowsMinFill, kGroupRowsOneStep
 // and kGroupRowsPackedRounds); long probability rows choose their chunk
-// size by launches and fill (kSplitFillMinPerCU).
+// size by launches and fill (kSplitSparseNum, kSplitThinPerCU).
 int library_shape(const float* x, const float* y, int64_t rows, int64_t cols, int em, int dev,
                   const DeviceFacts& f, Shape* out) {
   Shape s = default_shape(x, y, cols, em);
@@ -1175,8 +1170,7 @@ hipError_t run_plan(const Plan& p, const float* x, float* y, const int64_t* labe
         const int64_t ns = store_delay_ns(nb * cols * 4);
         delay = ns > 0 ? ns_to_ticks(ns, f) : 0;
       }
-      XchArgs xa{f.scratch, exchange_key(yb, nonce), p.limit_ticks, 1u,  // join
-                 entry_base(f, nb), 0u};
+      XchArgs xa{f.scratch, exchange_key(yb, nonce), p.limit_ticks, entry_base(f, nb)};
       void* args[] = {&xb, &yb, &xa, &cols, &ichunks, &delay, &c};
       const hipError_t e = launch(fn, nb * p.chunks, s.threads, args, st);
       if (e != hipSuccess) return e;
@@ -1191,15 +1185,12 @@ hipError_t run_plan(const Plan& p, const float* x, float* y, const int64_t* labe
     int64_t chunk = 0;
     int wpr = long_workgroups(nb, cols, f, &chunk);
     int entries = static_cast<int>(ceil_div(wpr, xch::kEntrySlots));
-    XchArgs xa{f.scratch, exchange_key(yb, nonce), p.limit_ticks, 1u,
-               entry_base(f, nb * entries), 0u};
+    XchArgs xa{f.scratch, exchange_key(yb, nonce), p.limit_ticks, entry_base(f, nb * entries)};
     void* a1[] = {&xb, &xa, &cols, &wpr, &entries, &chunk};
     hipError_t e = launch(fn_stats, nb * wpr, kLongThreads, a1, st);
     if (e != hipSuccess) return e;
-    int apr = wpr;
-    XchArgs xb2{f.scratch, xa.key, p.limit_ticks, 0u, xa.base, 0u};  // find only
-    void* a2[] = {&xb, &yb, &xb2, &cols, &wpr, &entries, &apr, &chunk, &c};
-    e = launch(fn, nb * apr, kLongThreads, a2, st);
+    void* a2[] = {&xb, &yb, &xa, &cols, &wpr, &entries, &chunk, &c};
+    e = launch(fn, nb * wpr, kLongThreads, a2, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -1328,7 +1319,7 @@ hipError_t run_nll(const float* x, float* y, const int64_t* labels, int64_t rows
   int64_t chunk = (ceil_div(cols, want) + 3) & ~int64_t(3);
   int chunks = static_cast<int>(ceil_div(cols, chunk));
   XchArgs xa{f.scratch, exchange_key(y, g_nonce.fetch_add(1, std::memory_order_relaxed)),
-             ns_to_ticks(int64_t(xch::kWaitLimitUs) * 1000, f), 1u, entry_base(f, rows), 0u};
+             ns_to_ticks(int64_t(xch::kWaitLimitUs) * 1000, f), entry_base(f, rows)};
   void* split_args[] = {&x, &labels, &y, &xa, &cols, &chunks, &chunk, &c};
   return launch(reinterpret_cast<const void*>(&k_nll_split<512, kNllStrips>), rows * chunks, 512,
                 split_args, st);

@@ -22,11 +22,10 @@ PROBE_API int probe_long_rows(const float* x, float* y, uint64_t* scratch, uint6
   if (rows * entries > xch::kMaxRowsPerLaunch) return -1;
   const Clip clip{kClipLo, kExpClipLo, kClipLo};
   const uint32_t grid = static_cast<uint32_t>(rows * wpr);
-  const XchArgs join{scratch, key, limit_ticks, 1u, base, 0u};
-  const XchArgs find{scratch, key, limit_ticks, 0u, base, 0u};
+  const XchArgs xa{scratch, key, limit_ticks, base};
   k_long_stats<kLongThreads, kExpAccurate>
-      <<<grid, kLongThreads, 0, stream>>>(x, join, cols, wpr, entries, chunk);
+      <<<grid, kLongThreads, 0, stream>>>(x, xa, cols, wpr, entries, chunk);
   k_long_apply<kLongThreads, kExpAccurate>
-      <<<grid, kLongThreads, 0, stream>>>(x, y, find, cols, wpr, entries, wpr, chunk, clip);
+      <<<grid, kLongThreads, 0, stream>>>(x, y, xa, cols, wpr, entries, chunk, clip);
   return static_cast<int>(hipGetLastError());
 }
