@@ -254,6 +254,25 @@ __device__ __forceinline__ float seg_sum(float v) {
   return v;
 }
 
+// The same over a wavefront in binary64, each half of a value moved by itself.
+__device__ __forceinline__ double wave_sum64(double v) {
+  auto halves = [](double x, auto move) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const float lo = move(__builtin_bit_cast(float, static_cast<uint32_t>(u)));
+    const float hi = move(__builtin_bit_cast(float, static_cast<uint32_t>(u >> 32)));
+    return __builtin_bit_cast(
+        double, static_cast<uint64_t>(__builtin_bit_cast(uint32_t, hi)) << 32 |
+                    static_cast<uint64_t>(__builtin_bit_cast(uint32_t, lo)));
+  };
+  v = v + halves(v, [](float x) { return dpp_mov<kDppQuadSwap1>(x); });
+  v = v + halves(v, [](float x) { return dpp_mov<kDppQuadSwap2>(x); });
+  v = v + halves(v, [](float x) { return dpp_mov<kDppHalfMirror>(x); });
+  v = v + halves(v, [](float x) { return dpp_mov<kDppMirror>(x); });
+  v = v + halves(v, [](float x) { return row16_partner(x); });
+  v = v + halves(v, [](float x) { return half32_partner(x); });
+  return v;
+}
+
 // Pairwise (tree) sum of a register array, depth ceil(log2 N): keeps the
 // per-lane rounding chain short on long rows.
 template <int N>

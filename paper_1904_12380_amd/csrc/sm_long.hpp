@@ -118,19 +118,23 @@ __global__ __launch_bounds__(NT) void k_long_apply(const float* x, float* y, Xch
 #pragma unroll
     for (int k = 1; k < kLongMaxEntries; ++k) m = fmaxf(m, decode_m(q[k]));
     m = seg_max<64>(m);
-    float s = 0.0f;
+    // In binary64: one rounding here is the same in all of the row's outputs.
+    double s = 0.0;
 #pragma unroll
     for (int k = 0; k < kLongMaxEntries; ++k)
-      s = s + decode_s(q[k]) * nll_rescale(decode_m(q[k]), m == kNegInf ? 0.0f : m);
-    s = seg_sum<64>(s);
+      s += static_cast<double>(decode_s(q[k])) *
+           static_cast<double>(nll_rescale(decode_m(q[k]), m == kNegInf ? 0.0f : m));
+    s = wave_sum64(s);
     if (tid == 0) {
+      const float last = MODE == kLogOut ? log_of_sum(static_cast<float>(s))
+                                         : static_cast<float>(1.0 / s);
       bcast[0] = found ? m : __builtin_nanf("");
-      bcast[1] = found ? s : __builtin_nanf("");
+      bcast[1] = found ? last : __builtin_nanf("");
     }
   }
   __syncthreads();
   const RowShift rs = row_shift(bcast[0], clip);
-  const float scale = MODE == kLogOut ? log_of_sum(bcast[1]) : 1.0f / bcast[1];
+  const float scale = bcast[1];  // ln S or 1 / S
   auto out = [&](float xv) {
     if constexpr (MODE == kLogOut)
       return log_out(xv, rs, scale);

@@ -59,8 +59,9 @@ def test_losses_of_long_structured_rows(kind):
 def test_two_pass_probabilities_of_a_repeating_row():
     """2^31 columns of alternating (0, v): 256 steps per workgroup.  Tolerance:
     half of the row's terms within 1.5 ulp (0.9e-7), 4 roundings of a step's tree
-    sum, one of the lane's sum, 16 of the merge's equal pairs (the sums over
-    lanes double equal values exactly), reciprocal and product: 1.5e-6."""
+    sum, one of the lane's sum and of its pair (equal values double exactly over
+    lanes, and the pairs merge in binary64), 1 / S, the exponential of the output
+    (1.8e-7) and the product: 8e-7."""
     cols = 1 << 31
     x = torch.empty(1, cols, device="cuda:0")
     y = torch.empty_like(x)
@@ -74,7 +75,7 @@ def test_two_pass_probabilities_of_a_repeating_row():
         for c, want in ((0, 1.0 / s), (cols - 1, math.exp(v32) / s), (cols // 2, 1.0 / s)):
             err = abs(float(y[0, c].double()) / want - 1.0)
             print(f"[sums]   column {c}: {err:.3e}", flush=True)
-            assert err <= 1.5e-6, (v, c, err)
+            assert err <= 8e-7, (v, c, err)
 
 
 # M - x is not an fp32 number: rounded to fp32 it is off by almost half an ulp
