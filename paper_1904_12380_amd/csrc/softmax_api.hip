@@ -68,34 +68,37 @@ constexpr int kBlockThreads = 1024;
 //    CU) its last round is part empty while the wavefront kernel still runs
 //    one: rows of up to 4096 columns lose there and keep the wavefront kernel
 //    (rows per CU: whole strips of 2048 columns 8 to 22, 3072 6 to 17, 4096 5
-//    to 13, up to 18%; ragged probability rows 8% at 8 to 13, from 3585 columns
-//    6 to 13 (2300 x 3901 15.3 against 16.1 us); ragged log rows of up to 2048
-//    columns 11% at 8 to 13);
-//  * rows of up to 1280 columns fill a third of its lanes' second strip: past 8
-//    per CU 3 to 12% slower (16000 x 1088 26.4 against 29.2 us; log rows level,
-//    ragged ones faster from 16), and whole strips 3 to 5% at 2 to 4;
+//    to 13, up to 18%; ragged probability rows 6% at 11 to 13, 9% at 8 to 13 of
+//    more than 3072 columns, from 3585 on at 6 to 13 (2300 x 3901 15.3 against
+//    16.1 us); ragged log rows of up to 1280 columns 8% at 8 to 16, of up to
+//    1536 5% at 8 to 13);
+//  * probability rows of up to 1120 columns leave most of its lanes' second
+//    strip empty: whole strips 2 to 13% slower past 8 per CU (16000 x 1088 26.4
+//    against 29.2 us), ragged ones 4 to 7% past 40;
 //  * ragged rows whose strips the 1024-thread kernel's two per lane hold (span
-//    6145 to 8192) lose 3 to 11% while every row has a place there, two per CU
+//    6145 to 8192) lose 3 to 15% while every row has a place there, two per CU
 //    (74 x 6803 5.5 against 6.2 us), and gain 10 to 27% on more;
-//  * against the split kernel, ragged rows of up to 20 strips gain from a third
-//    of a row per CU (18001 x 116 9.9 -> 8.7 us, x 3728 116 -> 100); whole
-//    strips while a CU holds all its rows, up to two (17000 x 400 14.0 -> 12.2),
-//    and between 3 and 6 per CU, where the split kernel takes a launch more
-//    than it fills (17000 x 1024 30.6 -> 27.8; but x 600 16.8 against 19.8);
-//    16384 columns, two full chunks, up to 23% slower (800 rows 18.5 against
-//    24.0); 21 to 24 strips lose up to 16% and gain 6% at most (600 x 24570
-//    22.3 against 26.6);
+//  * against the split kernel, whole strips gain at one to two rows per CU
+//    (17000 x 400 14.0 -> 12.2, 24000 x 400 16.0 -> 14.9, 16384 x 400 6%); up to
+//    20480 columns also between 3 and 6, where the split kernel takes a launch
+//    more than it fills (17000 x 1024 30.6 -> 27.8); elsewhere up to 30% slower
+//    (800 x 16384 18.5 against 24.0, 600 x 17000 16.8 against 19.8);
+//  * ragged probability rows of up to 20 strips gain from a third of a row per
+//    CU (18001 x 116 9.9 -> 8.7 us, x 3728 116 -> 100); of 21 to 24 strips 1 to
+//    6% at a half to 7/8 and past 4 but for 7 to 8, where the split kernel's
+//    launches are full (22001 x 1500 7%; 300 x 24573 9% slower, x 600 20%);
 //  * ragged log rows, whose split kernel has 32-bit access, gain from two per
 //    CU at any such length (18001 x 932 36.0 -> 26.8 us, 24573 x 1024 45.6 ->
 //    40.7).
 constexpr int kRowThreads = 256;
 constexpr int64_t kRowMinCols = 1088;
-constexpr int64_t kRowThinMaxCols = 1280;
+constexpr int64_t kRowThinMaxCols = 1120;
+constexpr int64_t kRowThinMaxColsLog = 1280;
+constexpr int64_t kRowBandMaxColsLog = 1536;
 constexpr int64_t kRowMaxCols = 10240;
 constexpr int64_t kRowMaxColsLog = 5120;
-constexpr int64_t kRowOverSplitMinCols = 16384;
-constexpr int64_t kRowOverSplitSpan = 20480;    // probability rows: 20 strips
-constexpr int64_t kRowOverSplitMaxSpan = 24576;  // log rows and a caller's plan: 24
+constexpr int64_t kRowOverSplitSpan = 20480;     // 20 strips
+constexpr int64_t kRowOverSplitMaxSpan = 24576;  // 24 strips
 // Probability and log rows longer than this take the one-pass split kernel
 // rather than one workgroup per row (measured with the dispatch sweep,
 // paper_1904_12380_amd/sweep.py).  Per 64 MiB of logits, 16384 columns ran
@@ -883,24 +886,32 @@ bool small_block_shape(const float* x, const float* y, int64_t rows, int64_t col
   bool take = false;
   if (cols < kRowMinCols) {
     take = false;
-  } else if (cols <= kRowThinMaxCols) {
-    take = ph && log ? !between(8, 16) : ph ? !above(8) : !above(8) && !between(2, 4);
   } else if (cols <= kWaveRowMaxCols) {
     if (ph && log)
-      take = cols > kWaveRowMaxColsScalar || !between(8, 13);
+      take = cols <= kRowThinMaxColsLog   ? !between(8, 16)
+             : cols <= kRowBandMaxColsLog ? !between(8, 13)
+                                          : true;
     else if (ph)
-      take = cols <= 3072 ? !between(11, 13) : cols <= 3584 ? !between(8, 13) : !between(6, 13);
+      take = cols <= kRowThinMaxCols ? !between(11, 13) && !above(40)
+             : cols <= 3072          ? !between(11, 13)
+             : cols <= 3584          ? !between(8, 13)
+                                     : !between(6, 13);
     else
-      take = cols <= kWaveRowMaxColsScalar ? !between(8, 22)
-             : cols <= 3072                ? !between(6, 17)
-                                           : !between(5, 13);
+      take = cols <= kRowThinMaxCols && !log ? !above(8)
+             : cols <= kWaveRowMaxColsScalar ? !between(8, 22)
+             : cols <= 3072                  ? !between(6, 17)
+                                             : !between(5, 13);
   } else if (cols <= kRowMaxCols) {
     take = log ? cols <= kRowMaxColsLog : !ph || span <= 6144 || span > 8192 || above(2);
-  } else if (cols > kRowOverSplitMinCols) {
-    take = log ? ph && rows >= 2 * f.cus
-           : span > kRowOverSplitSpan ? false
-           : ph                       ? 3 * rows >= f.cus
-                                      : between(1, 2) || between(3, 6);
+  } else if (cols > kSplitMinColsProb && cols < kRowOverSplitMaxSpan) {
+    if (log)
+      take = ph && rows >= 2 * f.cus;
+    else if (ph)
+      take = span <= kRowOverSplitSpan ? 3 * rows >= f.cus
+                                       : (2 * rows >= f.cus && 8 * rows <= 7 * f.cus) ||
+                                             (above(4) && !between(7, 8));
+    else
+      take = between(1, 2) || (cols > 16384 && cols <= kRowOverSplitSpan && between(3, 6));
   }
   if (!take) return false;
   return row_block_shape(x, y, cols, em, out);

@@ -33,8 +33,9 @@ WINDOWS = 7
 ROUNDS = 3
 ROTATE_BYTES = 1 << 30
 
-DEFAULT_COLS = (4, 8, 16, 32, 50, 64, 65, 100, 128, 129, 250, 256, 512, 1000, 1024, 2048, 4093,
-                4096, 8192, 16383, 16384, 32765, 32768, 65536, 131072)
+DEFAULT_COLS = (4, 8, 16, 32, 50, 64, 65, 100, 128, 129, 250, 256, 512, 1000, 1024, 1100, 1201,
+                2048, 2049, 3001, 4093, 4096, 5000, 6142, 7001, 8192, 9001, 10240, 16383, 16384,
+                17000, 18001, 24573, 32765, 32768, 65536, 131072)
 
 
 def candidates(cols: int) -> list[dict]:
@@ -45,10 +46,14 @@ def candidates(cols: int) -> list[dict]:
         out.append(dict(kernel_name="group_rows", vec_width=4))
     if cols <= 256:
         out += [dict(kernel_name="packed", vec_width=w) for w in (4, 1)]
-    if cols <= 4096:
+    if 32 <= cols <= 4096:
         out += [dict(kernel_name="wave_row", vec_width=w) for w in (4, 1)]
-    if cols <= 32768:
-        out += [dict(kernel_name="block_row", vec_width=w) for w in (4, 1)]
+    if 256 <= cols <= 32768:
+        out += [dict(kernel_name="block_row", vec_width=w, block_threads=1024) for w in (4, 1)]
+    if 1088 <= cols <= 24576:
+        # 256 threads per row; where the library has no such kernel for the
+        # row, the 1024-thread one runs under this plan too
+        out.append(dict(kernel_name="block_row", vec_width=4, block_threads=256))
     if cols >= 1024:
         for w in (4, 1):
             for nt, epl in ((256, 32), (512, 32), (512, 64)):
@@ -60,6 +65,8 @@ def candidates(cols: int) -> list[dict]:
 
 def label(plan: dict) -> str:
     s = f"{plan['kernel_name']}/v{plan['vec_width']}"
+    if plan["kernel_name"] == "block_row":
+        s += f"/{plan['block_threads']}"
     if plan["kernel_name"] == "split_row":
         s += f"/{plan['block_threads']}x{plan['elems_per_lane']}"
         s += "/sched" if plan.get("store_delay_ns", -1) < 0 else "/nodelay"
@@ -68,7 +75,7 @@ def label(plan: dict) -> str:
 
 def main(argv=None) -> int:
     ap = argparse.ArgumentParser(description=__doc__.splitlines()[0])
-    ap.add_argument("--mib", type=int, default=64, help="MiB of logits per call")
+    ap.add_argument("--mib", type=float, default=64, help="MiB of logits per call")
     ap.add_argument("--out", default=".", help="directory for sweep.json / sweep.md")
     ap.add_argument("--cols", default=None, help="comma-separated row lengths")
     args = ap.parse_args(argv)
@@ -109,7 +116,7 @@ def main(argv=None) -> int:
     results = []
     t_start = time.time()
     for cols in cols_list:
-        rows = max(1, (args.mib << 18) // cols)
+        rows = max(1, int(args.mib * (1 << 18)) // cols)
         nbytes = 8 * rows * cols
         n = max(2, -(-ROTATE_BYTES // nbytes))
         gen.manual_seed(1000 + cols)

@@ -107,20 +107,24 @@ def test_ten_strips_at_most(cols, threads):
 
 # columns, rows per CU (num / den, +1 row), kernel, threads: both sides of the
 # lines between the 256-thread kernel and the others.
-LINES = [(1100, 2, 1, 0, "block_row", 256), (1100, 2, 1, 1, "wave_row", 256),
-         (1280, 8, 1, 0, "block_row", 256), (1280, 8, 1, 1, "wave_row", 256),
-         (1201, 8, 1, 0, "block_row", 256), (1201, 8, 1, 1, "wave_row", 256),
-         (1284, 2, 1, 1, "block_row", 256), (1284, 8, 1, 1, "wave_row", 256),
+LINES = [(1100, 8, 1, 0, "block_row", 256), (1100, 8, 1, 1, "wave_row", 256),
+         (1120, 30, 1, 0, "wave_row", 256), (1124, 30, 1, 0, "block_row", 256),
+         (1117, 40, 1, 0, "block_row", 256), (1117, 40, 1, 1, "wave_row", 256),
+         (1121, 40, 1, 1, "block_row", 256), (1201, 11, 1, 1, "wave_row", 256),
          (3073, 8, 1, 0, "block_row", 256), (3073, 8, 1, 1, "wave_row", 256),
          (3585, 6, 1, 1, "wave_row", 256), (3585, 13, 1, 1, "block_row", 256),
          (6141, 1, 1, 0, "block_row", 256), (6142, 2, 1, 0, "block_row", 1024),
          (6142, 2, 1, 1, "block_row", 256), (8189, 2, 1, 0, "block_row", 1024),
          (8190, 2, 1, 0, "block_row", 256), (6144, 1, 1, 0, "block_row", 256),
-         (16384, 3, 2, 0, "split_row", 256), (16388, 3, 2, 0, "block_row", 256),
-         (20480, 5, 2, 0, "split_row", 256), (20480, 4, 1, 0, "block_row", 256),
-         (20480, 6, 1, 1, "split_row", 256), (20484, 3, 2, 0, "split_row", 256),
-         (20477, 1, 2, 0, "block_row", 256), (20478, 1, 2, 0, "split_row", 256),
-         (24573, 3, 1, 0, "split_row", 256)]
+         (16384, 2, 1, 0, "block_row", 256), (16384, 2, 1, 1, "split_row", 256),
+         (16384, 4, 1, 0, "split_row", 256), (16388, 4, 1, 0, "block_row", 256),
+         (20480, 5, 2, 0, "split_row", 256), (20480, 6, 1, 1, "split_row", 256),
+         (24572, 2, 1, 0, "block_row", 256), (24572, 4, 1, 0, "split_row", 256),
+         (24576, 2, 1, 0, "split_row", 256), (20477, 1, 2, -1, "block_row", 256),
+         (20478, 1, 2, -1, "split_row", 256), (20478, 1, 2, 0, "block_row", 256),
+         (24573, 7, 8, 0, "block_row", 256), (24573, 7, 8, 1, "split_row", 256),
+         (24573, 4, 1, 0, "split_row", 256), (24573, 4, 1, 1, "block_row", 256),
+         (24573, 8, 1, 0, "split_row", 256), (24573, 8, 1, 1, "block_row", 256)]
 
 
 @pytest.mark.parametrize("cols,num,den,more,kernel,threads", LINES)
@@ -141,8 +145,8 @@ def test_rows_over_the_split_kernel(cols):
 
 
 def test_a_plan_of_24_strips_still_runs():
-    """A caller's plan may ask for 256 threads on rows of 21 to 24 strips, which
-    the library itself gives to the split kernel."""
+    """A caller's plan may ask for 256 threads on rows of 21 to 24 strips whose
+    number the library itself gives to the split kernel."""
     for cols in (20484, 24000, 24570):
         print(f"[row-blocks] planned {cols}", flush=True)
         x = torch.randn(40, cols, device="cuda:0")
