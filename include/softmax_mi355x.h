@@ -74,11 +74,13 @@ extern "C" {
                                       is slower for the number of rows */
 #define SOFTMAX_KERNEL_BLOCK_ROW 3 /* cols <= 16380: one workgroup per row
                                       (256 threads from 1088 to 10240
-                                      columns, log outputs to 5120, else
-                                      1024); also rows of 16381 to 24576
-                                      columns, by their number and the
-                                      device, where the split grid's third
-                                      chunk would be partly empty */
+                                      columns, log outputs to 5120, except
+                                      ragged rows of 6142 to 8189 columns in
+                                      small numbers, else 1024); also rows of
+                                      16384 to 24575 columns, by their number
+                                      and the device, where they keep the
+                                      split grid's chunks or launches partly
+                                      empty */
 #define SOFTMAX_KERNEL_SPLIT_ROW 4 /* longer rows: several workgroups per row
                                       (chunks aligned to the row's phase for
                                       rows that are not whole strips) */
@@ -345,13 +347,16 @@ typedef struct softmax_plan_t {
 
 /* The shape fields (kernel, vec_width, lanes_per_row, elems_per_lane,
  * block_threads, chunks_per_row) depend only on the arguments, except that
- * rows of at most 256 columns choose between GROUP_ROWS, PACKED and
- * WAVE_ROW, long rows their chunk size, and rows of 16385 to 24575 columns between
- * BLOCK_ROW and SPLIT_ROW, by the device's resident workgroups or compute
- * units too;
- * grid, launches and store_delay_ns are those for the current device, and
- * 0 when no device is present (then the shape is the choice made from the
- * arguments alone).  No launch, no allocation (the first call on a device
+ * these choose by the number of rows and the device's resident workgroups or
+ * compute units too: rows of at most 256 columns between GROUP_ROWS, PACKED
+ * and WAVE_ROW; rows of 1088 to 4096 columns between WAVE_ROW and BLOCK_ROW;
+ * ragged rows of 6142 to 8189 columns between 256 and 1024 threads; rows of
+ * 16384 to 24575 columns between BLOCK_ROW and SPLIT_ROW; long rows their chunk
+ * size.  grid, launches and store_delay_ns are those for the current device,
+ * and 0 when no device is present.  The shape is then a choice made from x, y
+ * and cols alone, which the library need not take on a device: GROUP_ROWS up
+ * to 256 columns in whole strips, WAVE_ROW to 4096, 1024 threads per row to
+ * 16380, and no block rows past that.  No launch, no allocation (the first call on a device
  * queries its attributes). */
 SOFTMAX_API int softmax_plan(const float* x, const float* y, int64_t rows, int64_t cols,
                              softmax_plan_t* plan);
@@ -367,11 +372,13 @@ SOFTMAX_API int softmax_plan(const float* x, const float* y, int64_t rows, int64
  *                   32768) or _SPLIT_ROW (any cols);
  *   vec_width       4 (needs 16-byte aligned x and y and, above 256
  *                   columns, cols % 4 == 0, except the row-phase shapes
- *                   the library itself picks for rows that are not whole
- *                   strips: wave or block rows of 2049 to 8189 columns,
- *                   split rows whose phase adds no chunk) or 1;
- *   block_threads   one workgroup per row: 256 for the 256-thread kernel on
- *       rows that softmax_plan() gives it, anything else for 1024;
+ *                   for rows that are not whole strips: wave rows of 2049
+ *                   to 4093 columns, block rows of 1089 to 24573 (with
+ *                   256 threads; with 1024 of 2049 to 16377), split rows
+ *                   whose phase adds no chunk) or 1;
+ *   block_threads   block rows: 256 for the 256-thread kernel, where the
+ *                   library has it (16-byte aligned x and y, 1088 to 10240
+ *                   or 16381 to 24576 columns), anything else for 1024;
  *   block_threads, elems_per_lane   split rows only: 256 x 32 (chunks of
  *                   8192 columns), 512 x 32 (16384) or, with vec_width 4,
  *                   512 x 64 (32768); rows of more than 64 chunks take the

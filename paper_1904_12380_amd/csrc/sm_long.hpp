@@ -17,7 +17,7 @@
 // (64 workgroups per row, chunks held in registers one after another):
 // 8 x 4194304 81 -> 71 us (26.7 + 43.6, 6.1 TB/s in the second kernel),
 // 1 x 4194304 37 -> 18.7, 1 x 33554432 277 -> 75, 8 x 2000001 56 -> 40.6,
-// 20 x 2500000 130 -> 111.  No workgroup waits for another one of its
+// 20 x 2500000 130 -> 108.  No workgroup waits for another one of its
 // own kernel.  Rows may start at any 4-byte address: 128-bit loads and, where
 // x and y have the same phase, stores on the aligned strips, single columns
 // around them.

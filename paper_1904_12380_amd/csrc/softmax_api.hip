@@ -174,11 +174,15 @@ constexpr int64_t kLogPackedMinRowsPerCUUnaligned = 40;
 // 25.1 us so and 26.1 packed (65793 x 255 26.8 and 26.3, 129055 x 130 35.2
 // and 24.6).
 constexpr int64_t kLogPackedMaxCols = 224;
-// Log rows that are not whole strips: the row phase pays once the rows fill
-// the device (8188 x 2049 28.5 us against 48.2 with 32-bit access, 2795 x 6001
-// 25.3 against 30.6, 1023 x 2049 7.5 against 8.3; 512 x 4093 7.2 against 5.8,
-// 192 x 4093 6.8 against 4.3), and not in the split kernel, which keeps the
-// logits (559 x 30003 31.4 against 30.4 us, 41 x 50001 9.7 against 9.0).
+// Log rows that are not whole strips and too long for the 256-thread kernel
+// (kRowMaxColsLog): the row phase pays once the rows fill the device twice over.
+// Against 32-bit access, at 3 rows per CU and more: 900 x 6001 12.5 -> 11.3 us,
+// 2000 x 8189 28.6 -> 25.3, 768 x 16001 21.7 -> 19.2, 5000 x 12001 94.7 -> 80.9
+// (exactly 3 per CU of 6001 to 8190 columns 2 to 6% slower); below it the
+// 32-bit rows, one workgroup of 1024 threads each, are faster (512 x 4093 7.2
+// against 5.8 us, 192 x 4093 6.8 against 4.3, before those took 256 threads).
+// Not in the split kernel, which keeps the logits (559 x 30003 31.4 against
+// 30.4 us, 41 x 50001 9.7 against 9.0).
 constexpr int64_t kLogPhaseMinRowsPerCU = 3;
 
 // Split rows, one pass: a row spans at most this many workgroups (the
@@ -249,12 +253,11 @@ constexpr int64_t kBlockOverSplitMaxRowsDen = 16;
 // names them in 512 x 8 chunks.  Both kernels run up to four workgroups per CU
 // and group of rows (8 x 4194304: 2, 4 and 8 per CU within 3%; 1 x 33554432
 // slower by 20-70% with 8 and 16; a few more than are resident cost a second
-// round, 64 x 1048577 158 us with 17 a row and 149 with 16), at least one step
-// of columns each.  A group
-// holds up to 256 MiB of x, so that the second kernel finds as much of it as
-// can be in the memory-side cache: 3 x 16777217 ran 112 us in one group and
-// 188 in three, 32 x 4194304 264 us in groups of 256 MiB, 277 of 128 and 300
-// of 64.
+// round, 64 x 1048577 159 us with 17 a row and 149 with 16), at least one step
+// of columns each.  A group holds up to 256 MiB of x, so that the second kernel
+// finds as much of it as can be in the memory-side cache: 3 x 16777217 ran 112
+// us in one group and 188 in three, 32 x 4194304 264 us in groups of 256 MiB,
+// 277 of 128 and 300 of 64.
 constexpr int kSplitThreads = 512;
 constexpr int kSplitV = 8;
 constexpr int64_t kLongGroupBytes = int64_t(256) << 20;
@@ -703,7 +706,7 @@ Shape default_shape(const float* x, const float* y, int64_t cols, int em) {
 }
 
 // One workgroup of kRowThreads threads per row, with as many strips per lane
-// as the row needs: false where the library never takes such rows.
+// as the row needs: false where there is no such kernel for the row.
 bool row_block_shape(const float* x, const float* y, int64_t cols, int em, Shape* out) {
   const bool ph = cols % 4 != 0;
   const int64_t span = cols + (ph ? 3 : 0);  // what the strips must cover
@@ -1250,10 +1253,10 @@ constexpr int64_t kNllManyRowsPerCU = 4;
 // threads, so that up to four per CU (all that are resident: a few workgroups
 // more are a second round, 72 x 150008 14.8 us with 15 chunks a row and 13.7
 // with 14) share the launch's bytes in chunks of at least kNllSplitMinChunk
-// columns.  Measured split against the best single
-// workgroup per row: 64 x 262144 14.6 us (unsplit 20 and more), 30 x 50001
-// 6.4 against 7.0, 20 x 30003 5.6 and 5.6, 64 x 32768 6.3 against 5.3,
-// 100 x 50001 8.9 against 8.5, 200 x 131072 20.3 against 18.9.
+// columns.  Measured split against the best single workgroup per row: 64 x
+// 262144 14.6 us (unsplit 20 and more), 30 x 50001 6.4 against 7.0, 20 x 30003
+// 5.6 and 5.6, 64 x 32768 6.3 against 5.3, 100 x 50001 8.9 against 8.5, 200 x
+// 131072 20.3 against 18.9.
 constexpr int64_t kNllSplitCols = 32768;
 constexpr int64_t kNllSplitColsPerRow = 200;
 constexpr int64_t kNllSplitMinChunk = 8192;
